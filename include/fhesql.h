@@ -76,8 +76,10 @@ typedef struct tfhe_params {
 
 typedef struct tfhe_ctx tfhe_ctx;
 
-/* Blind-rotation kernel selection: the exact limb-split int8 MFMA external
- * product (default) or the plain scalar-integer one.  Both give identical bits. */
+/* Blind-rotation kernel selection: the fast kernels (default) -- exact
+ * products by double-precision transforms of key limbs for N = 1024 and 2048,
+ * by limb-split int8 MFMA otherwise -- or the plain scalar-integer one.  All
+ * give identical bits. */
 #define TFHE_KERNEL_MFMA 0
 #define TFHE_KERNEL_PLAIN 1
 
@@ -103,7 +105,11 @@ size_t tfhe_ksk_words(const tfhe_params* p);
  * has room, the BSK's 16-byte key windows (16 bytes per byte of the limb
  * form: 968 MB at n = 630, l = 3), from which the blind rotation reads its
  * A fragments directly; without room it stages the key in LDS instead (same
- * output bits).  With torus_bits = 32 it also keeps the key-switching table
+ * output bits).  With N = 1024 or 2048 it also holds the transforms of the
+ * BSK's limbs (16 bytes per coefficient pair and limb: 124 MB at n = 630,
+ * N = 1024, l = 3; 590 MB at n = 750, N = 2048, l = 4, torus_bits = 64), from
+ * which the transform blind rotation runs; without room the int8 kernels are
+ * used.  With torus_bits = 32 it also keeps the key-switching table
  * as int8 limbs (4 bytes per word, 84 MB at the standard set) for the MFMA
  * key switch; without room the key switch reads the word table.  Blocks
  * until the keys are on the device.  The context owns its copies; the
@@ -115,7 +121,9 @@ void tfhe_ctx_destroy(tfhe_ctx* ctx);
 const char* tfhe_last_error(const tfhe_ctx* ctx);
 /* Select TFHE_KERNEL_MFMA or TFHE_KERNEL_PLAIN for later blind rotations. */
 int tfhe_set_kernel(tfhe_ctx* ctx, int kind);
-/* Tuning knobs (none changes an output bit):
+/* Tuning knobs (none changes an output bit).  The row pass, the digit
+ * grouping and the split groups shape the int8 kernels: setting one of them
+ * away from its default runs the blind rotation on those, at any N:
  *   TFHE_TUNE_MAX_BATCH  maximum ciphertexts per blind-rotation launch when a
  *                        circuit level is split into launches (default 65536);
  *   TFHE_TUNE_ROW_PASS   MFMA kernel row tiles per pass (0 = default for N,

@@ -1,0 +1,863 @@
+// Blind rotation + sample extraction with exact negacyclic products by
+// double-precision transforms (gfx950), for rings of 1024 and 2048
+// coefficients.
+//
+// TFHE bootstrapping (ePrint 2018/421, Alg. 3 / Sec. 4): for i = 0..n-1,
+//   ACC <- ACC + ExtProd(BSK_i, X^{abar_i} ACC - ACC),
+// ExtProd(G, C)_v = sum_{u,p} Dec_p(C_u) * G[u*l+p-1][v] (negacyclic products).
+//
+// Why it is exact.  A real polynomial mod X^N + 1 is taken as M = N/2 complex
+// points a_j + i a_{j+M} mod X^M - i, whose M values are formed by radix-2
+// splittings X^{2m} - w^2 = (X^m - w)(X^m + w).  The key words are split into
+// balanced limbs (2 of 16 bits at q = 32, 3 of 22 bits at q = 64), each limb's
+// spectrum is kept in double precision, and the sums over the 2l digit
+// polynomials of every limb are transformed back and rounded to the nearest
+// integer.  Those sums are integers of magnitude at most
+// S = 2l 2^{bg-1} 2^{b-1} N (b = 16 or 22): 2^33.6 at n = 630, N = 1024,
+// l = 3, Bg = 2^7; at most 2^35.6 (q = 32) and 2^41.6 (q = 64) over every
+// parameter set a context accepts.  With u = 2^-53, a butterfly with its
+// twiddle held as (cos, tan) adds at most 6 u of its output's l2 norm going
+// forward and 7 u going back (twiddles accurate to 2 u), so that a transform
+// of 10 levels adds 60 u and 70 u, the accumulated products (2l + 2) 1.5 u,
+// and every output is within 60 u + 60 u + 96 u + 70 u < 300 u of S (Cauchy-
+// Schwarz over the digit and key polynomials): 2^-9 at q = 32 and 2^-3.2 at
+// q = 64, below the 1/2 at which rounding would go wrong, for any input.  So
+// every rounded value is the integer itself and the output bits are those of
+// the schoolbook product.
+//
+// Transform.  One wave transforms one polynomial with R = M/64 points per
+// lane: radix R in registers (uniform twiddles), an exchange through the
+// wave's own LDS buffer, radix R again, then the lane bits that are left but
+// one come into registers by lane swaps (v_permlane32_swap and
+// v_permlane16_swap) for another radix 4 (R = 8) or 2 (R = 16).  The last
+// radix-2 level is done by the thread that multiplies: it reads the pair from
+// the wave's buffer, so that a thread holds the same two frequencies of all G
+// ciphertexts and outputs of its workgroup, and each key value read from
+// memory serves G ciphertexts.  The inverse runs the same steps backwards.
+// A butterfly is 6 fused multiply-adds (x +- w y with w = c (1 + i t)).
+//
+// Workgroup: G ciphertexts, W waves, W/G polynomials of each at a time; the
+// accumulators stay in LDS, natural order, for all n steps.
+//
+// What it is for: the dense Toeplitz product on the int8 matrix cores ran at
+// 72% of their peak but needs 2N (k+1)l N limbs operations where the
+// transforms need about 1/100 of them.  Measured on one box, int8 path ->
+// this one, identical bits: n = 630, N = 1024, l = 3, q = 32: 1 ciphertext
+// 8.4 -> 3.5 ms, 256 30.8 -> 3.4 ms, 1024 50 -> 9.8 ms, 4096 77 -> 32 ms;
+// n = 750, N = 2048, l = 4, q = 64: 1 ciphertext 34 -> 18 ms, 256 158 -> 15 ms,
+// 1000 355 -> 61 ms.
+//
+// What bounds it: double-precision vector issue (a wave instruction takes
+// 4 cycles of its SIMD; about 4300 of them per ciphertext and step at
+// N = 1024, l = 3, q = 32) with two waves per SIMD to hide LDS and key latency.
+#include <algorithm>
+#include <cmath>
+
+#include "fhesql_internal.h"
+
+namespace {
+
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+template <int R>
+struct Plan {
+    static constexpr int L = R == 8 ? 3 : 4;  // log2 R
+    static constexpr int M = 64 * R, N = 128 * R;
+    static constexpr int NT2 = R / 2;             // twiddles of a radix-R pass in registers
+    static constexpr int NT3 = R == 8 ? 3 : 4;    // twiddles of the swapped levels
+    // twiddle table, (cos, tan) entries: second pass [R blocks][NT2], swapped
+    // levels [32 lane pairs][NT3], last level [M/2 pairs]
+    static constexpr int T3 = R * NT2;
+    static constexpr int T4 = T3 + 32 * NT3;
+    static constexpr int TN = T4 + M / 2;
+};
+
+template <typename T> struct Limb;
+template <> struct Limb<uint32_t> {
+    static constexpr int BITS = 16, COUNT = 2;
+};
+template <> struct Limb<uint64_t> {
+    static constexpr int BITS = 22, COUNT = 3;
+};
+
+// cos and tan of the first pass's angles (turns 1/8, 1/16, 1/32, 5/32, 1/64,
+// 9/64, 5/64, 13/64): the root of X^M - i
+constexpr double kC1[8] = {0.70710678118654752440, 0.92387953251128675613, 0.98078528040323044913,
+                           0.55557023301960222474, 0.99518472667219688624, 0.63439328416364549822,
+                           0.88192126434835502971, 0.29028467725446236764};
+constexpr double kT1[8] = {1.0, 0.41421356237309504880, 0.19891236737965800691, 1.49660576266548901760,
+                           0.09849140335716425308, 1.21850352558797634480, 0.53451113595079164109,
+                           3.29655820893832042688};
+
+// (x, y) -> (x + w y, x - w y), w = c (1 + i t), times i when ROT
+template <bool ROT>
+FHE_DEV void bf_fwd(double& xr, double& xi, double& yr, double& yi, double c, double t) {
+    const double a = __builtin_fma(-t, yi, yr), b = __builtin_fma(t, yr, yi);
+    const double pr = ROT ? -b : a, pi = ROT ? a : b;
+    yr = __builtin_fma(-c, pr, xr);
+    yi = __builtin_fma(-c, pi, xi);
+    xr = __builtin_fma(c, pr, xr);
+    xi = __builtin_fma(c, pi, xi);
+}
+
+// (x, y) -> (x + y, conj(w) (x - y))
+template <bool ROT>
+FHE_DEV void bf_inv(double& xr, double& xi, double& yr, double& yi, double c, double t) {
+    const double dr = xr - yr, di = xi - yi;
+    xr += yr;
+    xi += yi;
+    const double pr = c * __builtin_fma(t, di, dr), pi = c * __builtin_fma(-t, dr, di);
+    yr = ROT ? pi : pr;
+    yi = ROT ? -pr : pi;
+}
+
+// Radix-R pass in registers: level m (1..L) pairs indices R >> m apart; block
+// b of level m has the path bits b, its twiddle the index below and a factor
+// i when the last path bit is set.
+template <int R>
+FHE_DEV void lane_fwd(double (&re)[R], double (&im)[R], const double* c, const double* t) {
+    constexpr int L = Plan<R>::L;
+#pragma unroll
+    for (int m = 1; m <= L; m++) {
+        const int half = R >> m;
+#pragma unroll
+        for (int b = 0; b < (1 << (m - 1)); b++) {
+            const int k = m == 1 ? 0 : (1 << (m - 2)) + (b >> 1);
+#pragma unroll
+            for (int x = 0; x < half; x++) {
+                const int i = 2 * b * half + x, j = i + half;
+                if (b & 1) bf_fwd<true>(re[i], im[i], re[j], im[j], c[k], t[k]);
+                else bf_fwd<false>(re[i], im[i], re[j], im[j], c[k], t[k]);
+            }
+        }
+    }
+}
+
+template <int R>
+FHE_DEV void lane_inv(double (&re)[R], double (&im)[R], const double* c, const double* t) {
+    constexpr int L = Plan<R>::L;
+#pragma unroll
+    for (int m = L; m >= 1; m--) {
+        const int half = R >> m;
+#pragma unroll
+        for (int b = 0; b < (1 << (m - 1)); b++) {
+            const int k = m == 1 ? 0 : (1 << (m - 2)) + (b >> 1);
+#pragma unroll
+            for (int x = 0; x < half; x++) {
+                const int i = 2 * b * half + x, j = i + half;
+                if (b & 1) bf_inv<true>(re[i], im[i], re[j], im[j], c[k], t[k]);
+                else bf_inv<false>(re[i], im[i], re[j], im[j], c[k], t[k]);
+            }
+        }
+    }
+}
+
+// Exchange lane bit 5 (4) with the register bit that tells a from b.
+FHE_DEV void swap32(double& a, double& b) {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
+    const auto lo = __builtin_amdgcn_permlane32_swap(x.x, y.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(x.y, y.y, false, false);
+    a = __builtin_bit_cast(double, u2{lo[0], hi[0]});
+    b = __builtin_bit_cast(double, u2{lo[1], hi[1]});
+}
+FHE_DEV void swap16(double& a, double& b) {
+    typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+    u2 x = __builtin_bit_cast(u2, a), y = __builtin_bit_cast(u2, b);
+    const auto lo = __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+    a = __builtin_bit_cast(double, u2{lo[0], hi[0]});
+    b = __builtin_bit_cast(double, u2{lo[1], hi[1]});
+}
+
+template <int R>
+FHE_DEV void lane_swaps(double (&re)[R], double (&im)[R]) {
+#pragma unroll
+    for (int i = 0; i < R / 2; i++) {
+        swap32(re[i], re[i + R / 2]);
+        swap32(im[i], im[i + R / 2]);
+    }
+    if constexpr (R == 8) {
+#pragma unroll
+        for (int i = 0; i < R; i++)
+            if (!(i & 2)) {
+                swap16(re[i], re[i + 2]);
+                swap16(im[i], im[i + 2]);
+            }
+    }
+}
+
+// The levels after the swaps.  R = 8: register bits (b2, b1, e3), e3 the last
+// path bit of the second pass; R = 16: (b1, e2, e3, e4).
+template <int R>
+FHE_DEV void swapped_fwd(double (&re)[R], double (&im)[R], const double* c, const double* t) {
+    if constexpr (R == 8) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            if (i & 1) bf_fwd<true>(re[i], im[i], re[i + 4], im[i + 4], c[0], t[0]);
+            else bf_fwd<false>(re[i], im[i], re[i + 4], im[i + 4], c[0], t[0]);
+        }
+#pragma unroll
+        for (int f = 0; f < 2; f++)
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                const int i = 4 * f + e;
+                if (f) bf_fwd<true>(re[i], im[i], re[i + 2], im[i + 2], c[1 + e], t[1 + e]);
+                else bf_fwd<false>(re[i], im[i], re[i + 2], im[i + 2], c[1 + e], t[1 + e]);
+            }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            if (i & 1) bf_fwd<true>(re[i], im[i], re[i + 8], im[i + 8], c[i >> 1], t[i >> 1]);
+            else bf_fwd<false>(re[i], im[i], re[i + 8], im[i + 8], c[i >> 1], t[i >> 1]);
+        }
+    }
+}
+
+template <int R>
+FHE_DEV void swapped_inv(double (&re)[R], double (&im)[R], const double* c, const double* t) {
+    if constexpr (R == 8) {
+#pragma unroll
+        for (int f = 0; f < 2; f++)
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                const int i = 4 * f + e;
+                if (f) bf_inv<true>(re[i], im[i], re[i + 2], im[i + 2], c[1 + e], t[1 + e]);
+                else bf_inv<false>(re[i], im[i], re[i + 2], im[i + 2], c[1 + e], t[1 + e]);
+            }
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            if (i & 1) bf_inv<true>(re[i], im[i], re[i + 4], im[i + 4], c[0], t[0]);
+            else bf_inv<false>(re[i], im[i], re[i + 4], im[i + 4], c[0], t[0]);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            if (i & 1) bf_inv<true>(re[i], im[i], re[i + 8], im[i + 8], c[i >> 1], t[i >> 1]);
+            else bf_inv<false>(re[i], im[i], re[i + 8], im[i + 8], c[i >> 1], t[i >> 1]);
+        }
+    }
+}
+
+// LDS accesses of one wave are executed in order: only the compiler has to
+// keep a wave's writes before its reads.
+FHE_DEV void wave_order() {
+    __asm__ volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Workgroup barrier that orders LDS only (loads from global memory stay in flight).
+FHE_DEV void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// A wave's part of a transform: its twiddles and its byte offsets in LDS.
+// Exchange buffer: point j of block k.  At R = 8 the blocks are 66 points
+// apart, at R = 16 (whose buffers fill the LDS) 64 with j swizzled by k, so
+// that 16 neighbouring lanes touch 16 different 16-byte slots of the 256 bytes
+// that the LDS banks span, when they write (j varies) and when they read (k
+// and the lowest bit of j vary).  Pairs of the last level: member planes, the
+// second one shifted (R = 8) or swizzled (R = 16) by 8 points.
+// TWL: the twiddles stay in LDS and are read at each use (registers are
+// scarce there), else in registers.
+template <int R, bool TWL>
+struct WaveFft {
+    using P = Plan<R>;
+    static constexpr bool PAD = R == 8;
+    static constexpr int POINTS = PAD ? 528 : P::M;             // points of a buffer
+    static constexpr int PLANE = (P::M / 2 + (PAD ? 8 : 0));    // points of a member plane
+    double c2[TWL ? 1 : P::NT2], t2[TWL ? 1 : P::NT2], c3[TWL ? 1 : P::NT3], t3[TWL ? 1 : P::NT3];
+    uint8_t* lds;
+    uint32_t wb, rb, pb;  // write / read of the exchange, pairs
+    uint32_t tw2, tw3;    // this lane's twiddles (TWL)
+
+    // buf: offset of the wave's buffer; twl: offset of the LDS copy of the
+    // second pass's and the swapped levels' twiddles
+    FHE_DEV void init(const d2* tw, uint8_t* lds_, uint32_t buf, uint32_t twl) {
+        const int lane = threadIdx.x & 63;
+        const int k = (lane >> 1) & (R - 1);
+        const int bb = R == 8 ? (lane >> 5) * 4 + ((lane >> 4) & 1) * 2 + (lane & 1) : (lane >> 5) * 2 + (lane & 1);
+        lds = lds_;
+        wb = buf + lane * 16;
+        rb = buf + (PAD ? k * 66 + bb : k * 64 + (bb ^ ((k & 7) * 2))) * 16;
+        pb = buf + ((lane & 1) * PLANE + (PAD ? lane >> 1 : (lane >> 1) ^ ((lane & 1) * 8))) * 16;
+        if constexpr (TWL) {
+            tw2 = twl + k * P::NT2 * 16;
+            tw3 = twl + (P::T3 + (lane >> 1) * P::NT3) * 16;
+        } else {
+#pragma unroll
+            for (int i = 0; i < P::NT2; i++) {
+                const d2 w = tw[k * P::NT2 + i];
+                c2[i] = w.x;
+                t2[i] = w.y;
+            }
+#pragma unroll
+            for (int i = 0; i < P::NT3; i++) {
+                const d2 w = tw[P::T3 + (lane >> 1) * P::NT3 + i];
+                c3[i] = w.x;
+                t3[i] = w.y;
+            }
+        }
+    }
+    FHE_DEV d2& at(uint32_t off) const { return *(d2*)(lds + off); }
+    // (an opaque copy keeps the swizzled addresses from being held in
+    // registers across the step loop)
+    FHE_DEV static uint32_t opaque(uint32_t x) {
+        __asm__ volatile("" : "+v"(x));
+        return x;
+    }
+    FHE_DEV void put_blocks(const double (&re)[R], const double (&im)[R]) const {  // point `lane` of block r
+        const uint32_t b = opaque(wb);
+#pragma unroll
+        for (int r = 0; r < R; r++)
+            at(PAD ? b + r * 66 * 16 : (b ^ ((r & 7) * 32)) + r * 64 * 16) = d2{re[r], im[r]};
+    }
+    FHE_DEV void get_blocks(double (&re)[R], double (&im)[R]) const {
+        const uint32_t b = opaque(wb);
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const d2 v = at(PAD ? b + r * 66 * 16 : (b ^ ((r & 7) * 32)) + r * 64 * 16);
+            re[r] = v.x;
+            im[r] = v.y;
+        }
+    }
+    FHE_DEV void put_points(const double (&re)[R], const double (&im)[R]) const {  // points of this lane's block
+        const uint32_t b = opaque(rb);
+#pragma unroll
+        for (int r = 0; r < R; r++) at(PAD ? b + r * 8 * 16 : b ^ (r * 4 * 16)) = d2{re[r], im[r]};
+    }
+    FHE_DEV void get_points(double (&re)[R], double (&im)[R]) const {
+        const uint32_t b = opaque(rb);
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const d2 v = at(PAD ? b + r * 8 * 16 : b ^ (r * 4 * 16));
+            re[r] = v.x;
+            im[r] = v.y;
+        }
+    }
+    template <int K>
+    FHE_DEV void twiddles(uint32_t off, double (&c)[K], double (&t)[K]) const {
+#pragma unroll
+        for (int i = 0; i < K; i++) {
+            const d2 w = at(off + i * 16);
+            c[i] = w.x;
+            t[i] = w.y;
+        }
+    }
+
+    // points j = 64 r + lane in -> pairs of the last level in the buffer
+    FHE_DEV void forward(double (&re)[R], double (&im)[R]) const {
+        lane_fwd<R>(re, im, kC1, kT1);
+        put_blocks(re, im);
+        wave_order();
+        get_points(re, im);
+        if constexpr (TWL) {
+            double c[P::NT2], t[P::NT2], cs[P::NT3], ts[P::NT3];
+            twiddles(tw2, c, t);
+            lane_fwd<R>(re, im, c, t);
+            twiddles(tw3, cs, ts);
+            lane_swaps<R>(re, im);
+            swapped_fwd<R>(re, im, cs, ts);
+        } else {
+            lane_fwd<R>(re, im, c2, t2);
+            lane_swaps<R>(re, im);
+            swapped_fwd<R>(re, im, c3, t3);
+        }
+        wave_order();
+#pragma unroll
+        for (int r = 0; r < R; r++) at(pb + r * 32 * 16) = d2{re[r], im[r]};
+    }
+    // pairs in the buffer -> the first pass's inputs in registers
+    FHE_DEV void inverse_to_first(double (&re)[R], double (&im)[R]) const {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const d2 v = at(pb + r * 32 * 16);
+            re[r] = v.x;
+            im[r] = v.y;
+        }
+        if constexpr (TWL) {
+            double c[P::NT2], t[P::NT2], cs[P::NT3], ts[P::NT3];
+            twiddles(tw3, cs, ts);
+            swapped_inv<R>(re, im, cs, ts);
+            twiddles(tw2, c, t);
+            lane_swaps<R>(re, im);
+            lane_inv<R>(re, im, c, t);
+        } else {
+            swapped_inv<R>(re, im, c3, t3);
+            lane_swaps<R>(re, im);
+            lane_inv<R>(re, im, c2, t2);
+        }
+        wave_order();
+        put_points(re, im);
+        wave_order();
+        get_blocks(re, im);
+    }
+    FHE_DEV void inverse_first(double (&re)[R], double (&im)[R]) const { lane_inv<R>(re, im, kC1, kT1); }
+    // offset of member e of pair g in a buffer
+    FHE_DEV static uint32_t pair_off(int e, int g) { return (e * PLANE + (PAD ? g : g ^ (e * 8))) * 16; }
+};
+
+// -------------------------------------------------------- key spectra
+
+// fkey[poly][limb][member][pair]: spectrum of limb `limb` of key polynomial
+// `poly` = BSK[i][r][v], scaled by 1/M; member e of pair g as a thread of the
+// blind rotation reads them.  One wave per (poly, limb).
+template <typename T, int R>
+__global__ __launch_bounds__(64) void fft_key_kernel(const T* bsk, const d2* tw, d2* fkey) {
+    using P = Plan<R>;
+    using F = WaveFft<R, false>;
+    __shared__ d2 buf[F::POINTS];
+    const int lane = threadIdx.x;
+    const int limb = blockIdx.x % Limb<T>::COUNT;
+    const size_t poly = blockIdx.x / Limb<T>::COUNT;
+    const T* K = bsk + poly * P::N;
+    F f;
+    f.init(tw, (uint8_t*)buf, 0, 0);
+    auto part = [&](int j) -> double {
+        T x = K[j];
+        constexpr int b = Limb<T>::BITS;
+        int64_t v = 0;
+        for (int m = 0; m <= limb; m++) {
+            // the last limb holds the bits that are left, as a signed number
+            const int w = m + 1 < Limb<T>::COUNT ? b : Torus<T>::Q - b * (Limb<T>::COUNT - 1);
+            const int sh = 64 - w;
+            v = (int64_t)((uint64_t)x << sh) >> sh;
+            x = (T)((T)(x - (T)v) >> b);
+        }
+        return (double)v;
+    };
+    double re[R], im[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        re[r] = part(64 * r + lane);
+        im[r] = part(64 * r + lane + P::M);
+    }
+    f.forward(re, im);
+    __syncthreads();
+    d2* out = fkey + (size_t)blockIdx.x * P::M;
+    constexpr double scale = 1.0 / P::M;
+    for (int g = lane; g < P::M / 2; g += 64) {
+        const d2 x = f.at(F::pair_off(0, g)), y = f.at(F::pair_off(1, g)), w = tw[P::T4 + g];
+        double xr = x.x, xi = x.y, yr = y.x, yi = y.y;
+        bf_fwd<false>(xr, xi, yr, yi, w.x, w.y);
+        out[g] = d2{xr * scale, xi * scale};
+        out[P::M / 2 + g] = d2{yr * scale, yi * scale};
+    }
+}
+
+// ------------------------------------------------------ blind rotation
+
+struct FftArgs {
+    const void* lwe;          // [B][n+1] words
+    const d2* fkey;           // [n][2l][2][limbs][M]
+    const d2* tw;             // twiddle table
+    const void* tv;           // test polynomials [ntv][N] words
+    const int32_t* tv_index;  // [B] or null
+    void* out;                // [B][N+1] words
+    int B, n, l, bg_bits;
+};
+
+// One configuration: W waves and G ciphertexts per workgroup; KD: a thread's
+// ring of key values, in polynomials; KX of them are requested a transform
+// ahead, the others when the transform's registers are free.
+template <typename T_, int R_, int W_, int G_, int KD_, int KX_, bool TWL_>
+struct Cfg {
+    using T = T_;
+    static constexpr int R = R_, W = W_, G = G_, KD = KD_, KX = KX_;
+    static constexpr bool TWL = TWL_;
+    using P = Plan<R>;
+    using F = WaveFft<R, TWL>;
+    static constexpr uint32_t BUF = F::POINTS * 16;                       // bytes of a wave's buffer
+    static constexpr uint32_t ACC = W * BUF;                              // accumulators [G][2][N]
+    static constexpr uint32_t TW = ACC + G * 2 * P::N * (uint32_t)sizeof(T);  // twiddles (TWL)
+    static constexpr uint32_t LDS = TW + (TWL ? (uint32_t)P::T4 * 16 : 0);
+};
+
+template <typename CF>
+__global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(2, 2))) void br_fft_kernel(FftArgs a) {
+    using T = typename CF::T;
+    using P = typename CF::P;
+    using WF = typename CF::F;
+    constexpr int R = CF::R, W = CF::W, G = CF::G, KD = CF::KD, KX = CF::KX;
+    constexpr int N = P::N, M = P::M, LN = __builtin_ctz(N);
+    constexpr int Q = Torus<T>::Q;
+    constexpr int OUT = 2 * Limb<T>::COUNT;       // outputs: component, limb
+    constexpr int PPR = W / G;                    // polynomials of a ciphertext per round
+    constexpr int OS = 64 * W / (M / 2);          // thread sets that share the pairs' outputs
+    constexpr int OT = OUT / OS;                  // outputs of a thread
+    constexpr int IR = (OUT + PPR - 1) / PPR;     // inverse rounds
+    static_assert(W % G == 0 && 64 * W % (M / 2) == 0 && OUT % OS == 0, "work split");
+    static_assert(OS == 1 || PPR >= OUT, "one inverse round when the outputs are split over threads");
+    static_assert(PPR % KD == 0 && KX <= KD, "key ring");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = a.n, l = a.l, NB = 2 * l;
+    const int ct0 = blockIdx.x * G;
+
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    T* accs = (T*)(smem + CF::ACC);  // [G][2][N]
+
+    // this wave's ciphertext and its place among that ciphertext's waves
+    const int ct = wave % G, pq0 = wave / G;
+    const bool live = ct0 + ct < a.B;
+    const T* lwe = (const T*)a.lwe + (size_t)(live ? ct0 + ct : 0) * (n + 1);
+    T* const acc_ct = accs + (size_t)ct * 2 * N;
+
+    // accumulator = (0, X^{-bbar} testv)
+    for (int idx = tid; idx < G * N; idx += 64 * W) {
+        const int c = idx / N, j = idx & (N - 1);
+        const int gi = ct0 + c;
+        T body = 0;
+        if (gi < a.B) {
+            const int bb = (int)mod_switch<T>(((const T*)a.lwe)[(size_t)gi * (n + 1) + n], LN + 1);
+            const int e = (2 * N - bb) & (2 * N - 1);
+            const T* tv = (const T*)a.tv + (size_t)(a.tv_index ? a.tv_index[gi] : 0) * N;
+            body = monomial_coef<T>([&](int s) -> T { return tv[s]; }, N, e, j);
+        }
+        accs[(size_t)c * 2 * N + j] = 0;
+        accs[(size_t)c * 2 * N + N + j] = body;
+    }
+    if constexpr (CF::TWL)
+        for (int idx = tid; idx < P::T4; idx += 64 * W) ((d2*)(smem + CF::TW))[idx] = a.tw[idx];
+
+    WF f;
+    f.init(a.tw, smem, wave * CF::BUF, CF::TW);
+    const int g = tid & (M / 2 - 1), os = OS == 1 ? 0 : tid / (M / 2);
+    const d2 w4 = a.tw[P::T4 + g];
+    // this thread's pairs in buffer 0
+    const uint32_t px = WF::pair_off(0, g), py = WF::PAD ? px + WF::PLANE * 16 : WF::pair_off(1, g);
+
+    // gadget digits as in the int8 path: field p of z, read as a signed number
+    const int bgb = a.bg_bits;
+    const int shr = Q - l * bgb;
+    uint32_t off = 0;
+    for (int p = 0; p < l; p++) off += (uint32_t)(1 << (bgb - 1)) << (p * bgb);
+    const T F = (T)off << shr;
+    const T C = ((T)1 << (shr - 1)) + F;
+    const int fb = Q == 32 ? shr : shr - 32;
+
+    // digit words of X^{ab} ACC_u - ACC_u at coefficients 64 r + lane, r < 2R
+    auto form = [&](uint32_t (&z)[2 * R], int u, int ab) {
+        const T* acc = acc_ct + (size_t)u * N;
+        int x0 = lane;
+        __asm__ volatile("" : "+v"(x0));
+        const T* own = acc + x0;
+        x0 -= ab;
+#pragma unroll
+        for (int r = 0; r < 2 * R; r++) {
+            const int x = x0 + 64 * r;
+            const T v = acc[x & (N - 1)];
+            const T m = (T)(int64_t)(int32_t)__builtin_amdgcn_sbfe(x, LN, 1);  // all ones: negate
+            const T zz = (T)((T)(C - own[64 * r]) + (T)((v ^ m) - m)) ^ F;
+            z[r] = Q == 32 ? (uint32_t)zz : (uint32_t)((uint64_t)zz >> 32);
+        }
+    };
+    auto transform = [&](const uint32_t (&z)[2 * R], int p) {
+        const int pos = fb + (l - 1 - p) * bgb;
+        double re[R], im[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            re[r] = (double)(int)__builtin_amdgcn_sbfe((int)z[r], pos, bgb);
+            im[r] = (double)(int)__builtin_amdgcn_sbfe((int)z[R + r], pos, bgb);
+        }
+        f.forward(re, im);
+    };
+
+    // key values of this thread: 2 OT per polynomial, KD polynomials
+    const d2* const key0 = a.fkey + (size_t)os * OT * M + g;
+    d2 kv[KD][OT][2];
+    auto key_load = [&](d2 (&k)[OT][2], int i, int pq) {
+        const d2* kp = key0 + ((size_t)i * NB + pq) * (OUT * M);
+#pragma unroll
+        for (int o = 0; o < OT; o++)
+#pragma unroll
+            for (int e = 0; e < 2; e++) k[o][e] = kp[o * M + e * (M / 2)];
+    };
+    // the first KX polynomials of round (i, q0)
+    auto key_ahead = [&](int i, int q0) {
+#pragma unroll
+        for (int pp = 0; pp < KX; pp++)
+            if (q0 + pp < NB) key_load(kv[pp], i, q0 + pp);
+    };
+
+    constexpr double kMagic = 6755399441055744.0;  // 1.5 * 2^52: integers below 2^51 end up in the low bits
+    int abv = 0;  // abar of steps 64 (i/64) + lane
+    key_ahead(0, 0);
+    lds_barrier();
+    for (int i = 0; i < n; i++) {
+        if ((i & 63) == 0) abv = live && i + lane < n ? (int)mod_switch<T>(lwe[i + lane], LN + 1) : 0;
+        const int ab = __builtin_amdgcn_readlane(abv, i & 63);
+        double ar[OT][2][G], ai[OT][2][G];
+#pragma unroll
+        for (int o = 0; o < OT; o++)
+#pragma unroll
+            for (int e = 0; e < 2; e++)
+#pragma unroll
+                for (int c = 0; c < G; c++) ar[o][e][c] = ai[o][e][c] = 0;
+
+        // pairs of polynomial pp of every ciphertext
+        auto pairs = [&](d2 (&x)[G], d2 (&y)[G], int pp) {
+#pragma unroll
+            for (int c = 0; c < G; c++) {
+                x[c] = f.at(px + (pp * G + c) * CF::BUF);
+                y[c] = f.at(py + (pp * G + c) * CF::BUF);
+            }
+        };
+        auto products = [&](const d2 (&x)[G], const d2 (&y)[G], const d2 (&k)[OT][2]) {
+            double dr[2][G], di[2][G];
+#pragma unroll
+            for (int c = 0; c < G; c++) {
+                dr[0][c] = x[c].x;
+                di[0][c] = x[c].y;
+                dr[1][c] = y[c].x;
+                di[1][c] = y[c].y;
+                bf_fwd<false>(dr[0][c], di[0][c], dr[1][c], di[1][c], w4.x, w4.y);
+            }
+#pragma unroll
+            for (int o = 0; o < OT; o++)
+#pragma unroll
+                for (int e = 0; e < 2; e++)
+#pragma unroll
+                    for (int c = 0; c < G; c++) {
+                        ar[o][e][c] = __builtin_fma(dr[e][c], k[o][e].x, ar[o][e][c]);
+                        ai[o][e][c] = __builtin_fma(dr[e][c], k[o][e].y, ai[o][e][c]);
+                        ar[o][e][c] = __builtin_fma(-di[e][c], k[o][e].y, ar[o][e][c]);
+                        ai[o][e][c] = __builtin_fma(di[e][c], k[o][e].x, ai[o][e][c]);
+                    }
+        };
+
+        if constexpr (PPR == 1) {
+            for (int u = 0; u < 2; u++) {
+                uint32_t z[2 * R];
+                form(z, u, ab);
+                for (int p = 0; p < l; p++) {
+                    transform(z, p);
+                    key_load(kv[0], i, u * l + p);
+                    lds_barrier();
+                    d2 x[G], y[G];
+                    pairs(x, y, 0);
+                    lds_barrier();
+                    products(x, y, kv[0]);
+                }
+            }
+        } else {
+            for (int q0 = 0; q0 < NB; q0 += PPR) {
+                if (q0 + pq0 < NB) {
+                    const int u = q0 + pq0 >= l;
+                    uint32_t z[2 * R];
+                    form(z, u, ab);
+                    transform(z, q0 + pq0 - u * l);
+                }
+#pragma unroll
+                for (int pp = KX; pp < KD; pp++)
+                    if (q0 + pp < NB) key_load(kv[pp], i, q0 + pp);
+                lds_barrier();
+                const bool last = q0 + PPR >= NB;
+                const int ni = last ? (i + 1 < n ? i + 1 : 0) : i, nq = last ? 0 : q0 + PPR;
+#pragma unroll
+                for (int pp = 0; pp < PPR; pp++) {
+                    if (q0 + pp < NB) {
+                        d2 x[G], y[G];
+                        pairs(x, y, pp);
+                        products(x, y, kv[pp % KD]);
+                    }
+                    if (pp + KD < PPR) {
+                        if (q0 + pp + KD < NB) key_load(kv[pp % KD], i, q0 + pp + KD);
+                    } else if (pp + KD - PPR < KX) {
+                        if (nq + pp + KD - PPR < NB) key_load(kv[pp % KD], ni, nq + pp + KD - PPR);
+                    }
+                }
+                lds_barrier();
+            }
+        }
+
+        // back: one output of a ciphertext per wave and round
+#pragma unroll
+        for (int rd = 0; rd < IR; rd++) {
+#pragma unroll
+            for (int o = 0; o < OT; o++) {
+                if (OS == 1 && o / PPR != rd) continue;
+                const int slot = OS == 1 ? o % PPR : os * OT + o;
+#pragma unroll
+                for (int c = 0; c < G; c++) {
+                    bf_inv<false>(ar[o][0][c], ai[o][0][c], ar[o][1][c], ai[o][1][c], w4.x, w4.y);
+                    f.at(px + (slot * G + c) * CF::BUF) = d2{ar[o][0][c], ai[o][0][c]};
+                    f.at(py + (slot * G + c) * CF::BUF) = d2{ar[o][1][c], ai[o][1][c]};
+                }
+            }
+            lds_barrier();
+            const int o = rd * PPR + pq0;
+            const bool mine = OUT % PPR == 0 || o < OUT;
+            double re[R], im[R];
+            if (mine) f.inverse_to_first(re, im);
+            if (rd + 1 < IR) lds_barrier();
+            if (mine) {
+                f.inverse_first(re, im);
+                constexpr int LC = Limb<T>::COUNT;
+                T* acc = acc_ct + (size_t)(o / LC) * N + lane;
+                const int sh = (o % LC) * Limb<T>::BITS;
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    const uint64_t vr = __builtin_bit_cast(uint64_t, re[r] + kMagic) - __builtin_bit_cast(uint64_t, kMagic);
+                    const uint64_t vi = __builtin_bit_cast(uint64_t, im[r] + kMagic) - __builtin_bit_cast(uint64_t, kMagic);
+                    atomicAdd(acc + 64 * r, (T)vr << sh);
+                    atomicAdd(acc + 64 * r + M, (T)vi << sh);
+                }
+            }
+        }
+        // with one wave per ciphertext only that wave reads its accumulator
+        if (W > G) lds_barrier();
+        else wave_order();
+    }
+
+    // ---- sample extraction: a'_0 = A[0], a'_j = -A[N-j], b' = B[0]
+    lds_barrier();
+    T* out = (T*)a.out;
+    for (int c = 0; c < G && ct0 + c < a.B; c++) {
+        const T* A = accs + (size_t)c * 2 * N;
+        for (int j = tid; j <= N; j += 64 * W)
+            out[(size_t)(ct0 + c) * (N + 1) + j] = j == 0 ? A[0] : j < N ? (T)(0 - A[N - j]) : A[N];
+    }
+}
+
+template <typename CF>
+int launch_fft_t(tfhe_ctx* c, const FftArgs& a, hipStream_t s) {
+    auto k = br_fft_kernel<CF>;
+    static_assert(CF::LDS <= 160 * 1024, "LDS");
+    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)CF::LDS);
+    if (e != hipSuccess) return hip_check(c, e, "hipFuncSetAttribute(br_fft)");
+    hipLaunchKernelGGL(k, dim3((a.B + CF::G - 1) / CF::G), dim3(64 * CF::W), CF::LDS, s, a);
+    return hip_check(c, hipGetLastError(), "launch br_fft");
+}
+
+// cos and tan of `turns` (dyadic, never a quarter turn's odd multiple)
+d2 twiddle(long double turns) {
+    const long double x = 2.0L * 3.14159265358979323846264338327950288L * turns;
+    return d2{(double)cosl(x), (double)(sinl(x) / cosl(x))};
+}
+
+// Angles (in turns): after t levels the block with path bits d1..dt is mod
+// X^m - e^{2 pi i theta}, theta = 1/(4 2^t) + sum_i d_i 2^{i-1-t}, and the next
+// level's twiddle has the angle theta/2.
+template <int R>
+std::vector<d2> twiddle_table() {
+    using P = Plan<R>;
+    std::vector<d2> tw(P::TN);
+    auto theta = [](std::vector<int> d) {
+        const int t = (int)d.size();
+        long double x = 0.25L;
+        for (int i = 0; i < t; i++) x += d[i] * (long double)(1 << i);
+        return x / (long double)(1 << t);
+    };
+    auto bits = [](std::vector<int>& d, int v, int count) {  // first path bit = top bit
+        for (int b = count - 1; b >= 0; b--) d.push_back((v >> b) & 1);
+    };
+    for (int k = 0; k < R; k++)
+        for (int m = 1; m <= P::L; m++)
+            for (int q = 0; q < (m == 1 ? 1 : 1 << (m - 2)); q++) {
+                std::vector<int> d;
+                bits(d, k, P::L);
+                if (m > 1) {
+                    bits(d, q, m - 2);
+                    d.push_back(0);
+                }
+                tw[(size_t)k * P::NT2 + (m == 1 ? 0 : (1 << (m - 2)) + q)] = twiddle(theta(d) / 2);
+            }
+    for (int x = 0; x < 32; x++)
+        for (int q = 0; q < P::NT3; q++) {
+            std::vector<int> d;
+            bits(d, x & (R - 1), P::L);  // first pass
+            if (R == 8) {
+                bits(d, x >> 3, 2);               // e1 e2
+                d.push_back(q == 2 ? 1 : 0);      // e3 (a factor i for the first swapped level)
+                if (q) d.push_back(0);            // f1 (a factor i for the second)
+            } else {
+                d.push_back(x >> 4);  // e1
+                bits(d, q, 2);        // e2 e3
+                d.push_back(0);       // e4 (a factor i)
+            }
+            tw[P::T3 + (size_t)x * P::NT3 + q] = twiddle(theta(d) / 2);
+        }
+    for (int g = 0; g < P::M / 2; g++) {
+        const int r = g >> 5, x = g & 31;
+        std::vector<int> d;
+        bits(d, x & (R - 1), P::L);
+        if (R == 8) {
+            bits(d, x >> 3, 2);
+            d.push_back(r & 1);
+            bits(d, r >> 1, 2);  // f1 f2
+        } else {
+            d.push_back(x >> 4);
+            bits(d, r & 7, 3);       // e2 e3 e4
+            d.push_back(r >> 3);     // f1
+        }
+        tw[P::T4 + g] = twiddle(theta(d) / 2);
+    }
+    return tw;
+}
+
+template <typename T, int R>
+int setup_t(tfhe_ctx* c, hipStream_t s) {
+    using P = Plan<R>;
+    const std::vector<d2> tw = twiddle_table<R>();
+    const size_t polys = (size_t)c->p.n * 2 * c->p.l * 2;
+    const size_t key_bytes = polys * Limb<T>::COUNT * P::M * sizeof(d2);
+    if (hipMalloc(&c->d_fkey, key_bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        c->d_fkey = nullptr;
+        return TFHE_OK;
+    }
+    int rc;
+    if ((rc = hip_check(c, hipMalloc(&c->d_ftw, tw.size() * sizeof(d2)), "hipMalloc twiddles")) ||
+        (rc = hip_check(c, hipMemcpy(c->d_ftw, tw.data(), tw.size() * sizeof(d2), hipMemcpyHostToDevice),
+                        "copy twiddles")))
+        return rc;
+    auto k = fft_key_kernel<T, R>;
+    hipLaunchKernelGGL(k, dim3((unsigned)(polys * Limb<T>::COUNT)), dim3(64), 0, s, (const T*)c->d_bsk,
+                       (const d2*)c->d_ftw, (d2*)c->d_fkey);
+    return hip_check(c, hipGetLastError(), "launch fft_key");
+}
+
+}  // namespace
+
+// Key spectra and twiddles of a context whose ring has 1024 or 2048
+// coefficients (none without room for them: the int8 path is used then).
+int fft_setup(tfhe_ctx* c, hipStream_t s) {
+    if (c->p.N == 1024) return c->q == 32 ? setup_t<uint32_t, 8>(c, s) : setup_t<uint64_t, 8>(c, s);
+    if (c->p.N == 2048) return c->q == 32 ? setup_t<uint32_t, 16>(c, s) : setup_t<uint64_t, 16>(c, s);
+    return TFHE_OK;
+}
+
+bool fft_usable(const tfhe_ctx* c) {
+    return c->d_fkey && c->row_pass == 0 && c->digit_blocks == 0 && c->split_groups < 0;
+}
+
+int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index, void* big_out, uint32_t B,
+                  hipStream_t s) {
+    FftArgs a;
+    a.lwe = lwe_in;
+    a.fkey = (const d2*)c->d_fkey;
+    a.tw = (const d2*)c->d_ftw;
+    a.tv = tv;
+    a.tv_index = tv_index;
+    a.out = big_out;
+    a.B = (int)B;
+    a.n = (int)c->p.n;
+    a.l = (int)c->p.l;
+    a.bg_bits = (int)c->p.bg_bits;
+    // Up to 256 ciphertexts (a CU each) one per workgroup, then two, while
+    // that keeps every one resident; four above, two workgroups per CU, which
+    // quarters the key reads (N = 1024, 512 ciphertexts: 5.3 ms at two per
+    // workgroup; 1024: 9.8 ms at four, 32.2 ms for 4096).
+    //                 T         R  W  G KD KX TWL
+    if (c->q == 32) {
+        if (c->p.N == 2048) return launch_fft_t<Cfg<uint32_t, 16, 8, 1, 2, 1, false>>(c, a, s);
+        if (B > 512) return launch_fft_t<Cfg<uint32_t, 8, 4, 4, 1, 0, true>>(c, a, s);
+        if (B > 256) return launch_fft_t<Cfg<uint32_t, 8, 8, 2, 4, 4, false>>(c, a, s);
+        return launch_fft_t<Cfg<uint32_t, 8, 8, 1, 8, 8, false>>(c, a, s);
+    }
+    if (c->p.N == 2048) return launch_fft_t<Cfg<uint64_t, 16, 8, 1, 2, 1, false>>(c, a, s);
+    return launch_fft_t<Cfg<uint64_t, 8, 8, 1, 4, 4, false>>(c, a, s);
+}

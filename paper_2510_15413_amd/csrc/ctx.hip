@@ -9,6 +9,10 @@
 
 int launch_br_mfma(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index,
                    void* big_out, uint32_t B, void* ws, size_t ws_cap, hipStream_t s);
+int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index, void* big_out, uint32_t B,
+                  hipStream_t s);
+bool fft_usable(const tfhe_ctx* c);
+int fft_setup(tfhe_ctx* c, hipStream_t s);
 int launch_br_plain(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index,
                     void* big_out, uint32_t B, hipStream_t s);
 size_t mfma_ws_bytes(const tfhe_ctx* c, uint32_t B);
@@ -260,7 +264,7 @@ extern "C" int tfhe_ctx_create(const tfhe_params* p, const void* bsk, size_t bsk
         tfhe_ctx_destroy(c);
         return rc;
     }
-    if ((rc = launch_bsk_limbs(c, 0))) { tfhe_ctx_destroy(c); return rc; }
+    if ((rc = launch_bsk_limbs(c, 0)) || (rc = fft_setup(c, 0))) { tfhe_ctx_destroy(c); return rc; }
     if (c->q == 32) {
         // the MFMA key switch's limb table (4 bytes per word: 84 MB at the
         // standard set); without room the key switch reads the word table
@@ -326,6 +330,8 @@ extern "C" void tfhe_ctx_destroy(tfhe_ctx* c) {
     if (c->d_bsk) hipFree(c->d_bsk);
     if (c->d_bsk8) hipFree(c->d_bsk8);
     if (c->d_win) hipFree(c->d_win);
+    if (c->d_fkey) hipFree(c->d_fkey);
+    if (c->d_ftw) hipFree(c->d_ftw);
     if (c->d_ksk) hipFree(c->d_ksk);
     if (c->d_ksk8) hipFree(c->d_ksk8);
     if (c->d_gate_tv) hipFree(c->d_gate_tv);
@@ -484,6 +490,7 @@ int launch_blind_rotate(tfhe_ctx* c, const void* lwe_in, const void* testv_table
     const void* tv = testv_table ? testv_table : c->d_gate_tv;
     TimedLaunch tl(c, s, 0, B);
     if (c->kernel == TFHE_KERNEL_PLAIN) return launch_br_plain(c, lwe_in, tv, tv_index, big_out, B, s);
+    if (fft_usable(c)) return launch_br_fft(c, lwe_in, tv, tv_index, big_out, B, s);
     return launch_br_mfma(c, lwe_in, tv, tv_index, big_out, B, ws, ws_cap, s);
 }
 

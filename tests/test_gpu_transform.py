@@ -1,0 +1,114 @@
+"""The transform blind rotation (rings of 1024 and 2048 coefficients): bit for
+bit the int8 path on every ciphertext and the oracle on a few, at the edges of
+its launch shapes (one, two or four ciphertexts per workgroup, ragged last
+workgroup) and of the gadget (one level, an odd count, more polynomials than
+waves, one-bit and eight-bit digits), on inputs at the rounding boundaries,
+and with keys and digits of the largest magnitude (the transforms' rounding
+error bound is closest there)."""
+import sys
+
+import numpy as np
+import pytest
+
+import oracle
+import seeded_inputs as si
+from helpers import edge_lwe
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2510_15413_amd as fs  # noqa: E402
+from gpu_util import to_dev, from_dev, empty  # noqa: E402
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def both_paths(p, ctx, d, tv=None):
+    """Outputs of the default (transform) path and of the int8 path."""
+    got, ref = empty(p, d.shape[0], p.N + 1), empty(p, d.shape[0], p.N + 1)
+    ctx.tfhe_bootstrap_batch(d, got, testv=tv)
+    ctx.set_tuning(split_groups=1 << 20)
+    ctx.tfhe_bootstrap_batch(d, ref, testv=tv)
+    ctx.set_tuning(split_groups=-1)
+    torch.cuda.synchronize()
+    return got, ref
+
+
+@pytest.mark.parametrize("q,N,l,bg", [(32, 1024, 3, 7), (32, 1024, 1, 8), (32, 1024, 5, 6), (32, 1024, 31, 1),
+                                      (32, 2048, 3, 8), (32, 2048, 5, 6), (64, 1024, 4, 6), (64, 1024, 1, 8),
+                                      (64, 2048, 4, 6), (64, 2048, 3, 8), (64, 2048, 5, 6), (64, 2048, 1, 1)])
+def test_transform_path_parity(q, N, l, bg):
+    p = si.Params(f"t{q}_{N}", q, 5, 1, N, bg, l, 2, 8, 20, 25)
+    bsk = si.torus(7, 71 + l, p.bsk_words(), q)
+    ksk = np.zeros(p.ksk_words(), dtype=np.uint64)
+    ctx = fs.Context(p, bsk, ksk)
+    tv = oracle.gate_testv(p)
+    edge = edge_lwe(p, 72)
+    for B in (1, 2, 3, 257, 515):
+        lwe = si.torus(B, 73, B * (p.n + 1), q).reshape(B, p.n + 1)
+        if B > len(edge):
+            lwe[1:1 + len(edge)] = edge
+        say("transform", q, N, l, bg, "B =", B)
+        got, ref = both_paths(p, ctx, to_dev(p, lwe))
+        assert torch.equal(got, ref), (q, N, l, bg, B)
+        if B <= 3:
+            g = from_dev(p, got)
+            assert np.array_equal(g[B - 1], oracle.bootstrap(p, bsk, lwe[B - 1], tv)), (q, N, l, bg, B)
+    ctx.close()
+
+
+@pytest.mark.parametrize("q,N,l,bg", [(32, 1024, 3, 7), (32, 2048, 3, 8), (64, 1024, 3, 8), (64, 2048, 4, 6),
+                                      (64, 2048, 3, 8)])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_transform_path_largest_sums(q, N, l, bg, sign):
+    """Every key limb at the end of its range and, in the first step, every
+    digit of the body component at -Bg/2 (the accumulator is half the largest
+    negative decomposition and the rotation X^N = -1 doubles it)."""
+    M = (1 << q) - 1
+    p = si.Params(f"x{q}_{N}", q, 3, 1, N, bg, l, 2, 8, 20, 25)
+    widths = (16, 16) if q == 32 else (22, 22, 20)
+    word, sh = 0, 0
+    for w in widths:
+        word += (-(1 << (w - 1)) if sign < 0 else (1 << (w - 1)) - 1) << sh
+        sh += w
+    bsk = np.full(p.bsk_words(), word & M, dtype=np.uint64)
+    ctx = fs.Context(p, bsk, np.zeros(p.ksk_words(), dtype=np.uint64))
+    off = sum((1 << (bg - 1)) << (i * bg) for i in range(l)) << (q - l * bg)
+    tv = np.full(N, off >> 1, dtype=np.uint64)
+    for B in (1, 300, 600):
+        lwe = si.torus(B, 74, B * (p.n + 1), q).reshape(B, p.n + 1)
+        lwe[:, 0] = 1 << (q - 1)  # abar = N
+        lwe[:, p.n] = 0
+        say("largest sums", q, N, l, bg, sign, "B =", B)
+        got, ref = both_paths(p, ctx, to_dev(p, lwe), tv=to_dev(p, tv))
+        assert torch.equal(got, ref), (q, N, l, bg, B)
+        assert np.array_equal(from_dev(p, got)[0], oracle.bootstrap(p, bsk, lwe[0], tv))
+    ctx.close()
+
+
+def test_transform_path_look_ups_per_ciphertext():
+    """Per-ciphertext test polynomials (radix look-ups) at the 2048-coefficient
+    64-bit ring: compare and select of a few rows equal the int8 path's."""
+    p = si.Params("tlut", 64, 9, 1, 2048, 6, 4, 3, 6, 20, 51)
+    _, _, bsk, ksk = fs.tfhe_keygen(p, si.KEY_SEED_BASE + 75)
+    ctx = fs.Context(p, bsk, ksk)
+    rows, nb = 5, 3
+    col = to_dev(p, si.torus(1, 76, rows * nb * (p.n + 1), 64).reshape(rows, nb, p.n + 1))
+    lit = to_dev(p, si.torus(2, 76, nb * (p.n + 1), 64).reshape(nb, p.n + 1))
+    outs = []
+    for split in (-1, 1 << 20):
+        ctx.set_tuning(split_groups=split)
+        m, o = empty(p, rows, p.n + 1), empty(p, rows, nb, p.n + 1)
+        ctx.sql_radix_mask_scan(col, rows, nb, "lt", lit, m)
+        ctx.sql_radix_masked_select(m, col, rows, nb, o)
+        torch.cuda.synchronize()
+        outs.append((m, o))
+    ctx.set_tuning(split_groups=-1)
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+    ctx.close()
