@@ -29,6 +29,15 @@
 // the batch's inputs (each XCD then fetches only its tiles' columns of the
 // table, whose rows start on 128-byte lines), group-major otherwise (each XCD
 // fetches only its groups' inputs).
+//
+// Small batches.  A few ciphertexts fill only one group of workgroups (40 at
+// n = 630, 47 at n = 750), each with a serial chain of kN t 2^b / 64 chunks (or
+// kN coefficients) whose table reads come from HBM one after another.  So the
+// chain is cut into slices, a few per CU; a slice adds its sums to the outputs
+// with atomic adds (exact mod 2^q in any order), which the digit pre-pass has
+// set to (0^n, b').
+#include <algorithm>
+
 #include "fhesql_internal.h"
 
 namespace {
@@ -55,10 +64,20 @@ struct Vec16<uint64_t> {
 // the coefficient-major digit array.
 template <typename T, typename D>
 __global__ __launch_bounds__(THREADS) void ks_digits_kernel(const T* __restrict__ big, D* __restrict__ dig, int B,
-                                                            int kN, int tb) {
+                                                            int kN, int tb, int n, T* out, const uint64_t* out_ptrs,
+                                                            int set_out) {
     __shared__ uint32_t blk[64][65];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int i0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+    if (set_out) {
+        // outputs (0^n, b') of the block's ciphertexts, words split over gridDim.x blocks
+        const int per = (n + (int)gridDim.x) / (int)gridDim.x;
+        const int k0 = blockIdx.x * per, k1 = min(k0 + per, n + 1);
+        for (int c = c0 + w; c < min(c0 + 64, B); c += THREADS / 64) {
+            T* dst = out_ptrs ? (T*)(uintptr_t)out_ptrs[c] : out + (size_t)c * (n + 1);
+            for (int k = k0 + lane; k < k1; k += 64) dst[k] = k == n ? big[(size_t)c * (kN + 1) + kN] : (T)0;
+        }
+    }
 #pragma unroll
     for (int m = 0; m < 16; m++) {
         const int r = w + 4 * m, c = c0 + r, i = i0 + lane;
@@ -76,9 +95,38 @@ struct KsPlace {
     int tiles, groups;  // word tiles and ciphertext groups
     int per;            // workgroups per XCD run (the grid is 8 * per)
     int tile_major;     // 1: runs of consecutive tiles, 0: runs of consecutive groups
+    int slices;         // slices of the sum; more than one: added to the outputs atomically
 };
 
-template <typename T, typename D, int V, int WPW, int P>
+// Slices of a sum of `steps` serial steps whose launch has `wgs` workgroups:
+// `per_cu` workgroups per CU (4 of the MFMA form, 8 of the gather kernel, whose
+// steps are shorter reads), at least 8 steps each.  A launch that fills the
+// CUs by itself gains nothing (n = 630, 1024 ciphertexts: 316 us either way).
+// Measured, one slice -> this: n = 630, N = 1024 (q = 32) 1 ciphertext
+// 241 -> 32 us, 77 260 -> 55 us, 300 266 -> 92 us; n = 64, N = 256 1 ciphertext
+// 45 -> 14 us; n = 750, N = 2048 (q = 64) 1 ciphertext 3270 -> 290 us, 40
+// 3273 -> 341 us, 1000 3330 -> 1295 us.  Two per CU: 37, 52, 104, 14, 378, 393,
+// 1868 us.
+int ks_slices(const tfhe_ctx* c, int wgs, int steps, int per_cu) {
+    const int cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
+    if (wgs >= cus) return 1;
+    return std::max(1, std::min(per_cu * cus / wgs, steps / 8));
+}
+
+// (tile, group, slice) of a workgroup: L runs on XCD L % 8 as the (L / 8)-th
+// of that XCD's run; false for the padding of the last run.
+template <bool SPLIT>
+FHE_DEV bool ks_place(const KsPlace& pl, int& tile, int& grp, int& slice) {
+    const int z0 = (int)(blockIdx.x % 8) * pl.per + (int)(blockIdx.x / 8);
+    if (z0 >= pl.tiles * pl.groups * (SPLIT ? pl.slices : 1)) return false;
+    slice = SPLIT ? z0 % pl.slices : 0;
+    const int z = SPLIT ? z0 / pl.slices : z0;
+    tile = pl.tile_major ? z / pl.groups : z % pl.tiles;
+    grp = pl.tile_major ? z % pl.groups : z / pl.tiles;
+    return true;
+}
+
+template <typename T, typename D, int V, int WPW, int P, bool SPLIT>
 __global__ __launch_bounds__(THREADS) void keyswitch_kernel(const T* __restrict__ big, const D* __restrict__ dig,
                                                             const T* __restrict__ ksk, T* out,
                                                             const uint64_t* out_ptrs, int B, int n, int kN, int t,
@@ -90,11 +138,12 @@ __global__ __launch_bounds__(THREADS) void keyswitch_kernel(const T* __restrict_
     T* tab = (T*)smem;                       // [2][P][t*V][RS]
     const int TS = t * V * RS;               // words per coefficient
     const int tid = threadIdx.x;
-    // workgroup L runs on XCD L % 8 as the (L / 8)-th of that XCD's run
-    const int z = (int)(blockIdx.x % 8) * pl.per + (int)(blockIdx.x / 8);
-    if (z >= pl.tiles * pl.groups) return;  // padding of the last run
-    const int tile = pl.tile_major ? z / pl.groups : z % pl.tiles;
-    const int grp = pl.tile_major ? z % pl.groups : z / pl.tiles;
+    int tile, grp, slice;
+    if (!ks_place<SPLIT>(pl, tile, grp, slice)) return;
+    // this slice's coefficients, a multiple of P of them
+    const int cps = SPLIT ? (kN / P + pl.slices - 1) / pl.slices * P : kN;
+    const int ib = SPLIT ? slice * cps : 0, ie = SPLIT ? min(ib + cps, kN) : kN;
+    if (SPLIT && ib >= ie) return;
     const int c = grp * TC + tid;
     const int w0 = tile * WPW;
     const size_t row = (size_t)ks_row;  // table row stride in words
@@ -104,7 +153,7 @@ __global__ __launch_bounds__(THREADS) void keyswitch_kernel(const T* __restrict_
 
     T acc[WPW];
 #pragma unroll
-    for (int k = 0; k < WPW; k++) acc[k] = (w0 + k == n && live) ? big[(size_t)c * (kN + 1) + kN] : (T)0;
+    for (int k = 0; k < WPW; k++) acc[k] = (!SPLIT && w0 + k == n && live) ? big[(size_t)c * (kN + 1) + kN] : (T)0;
 
     // Subtract the rows that coefficient value r selects, from the rows of
     // one coefficient staged at cbuf.
@@ -140,14 +189,14 @@ __global__ __launch_bounds__(THREADS) void keyswitch_kernel(const T* __restrict_
             if (e < E) tab[(size_t)(BUF) * TS + (e / WPW) * RS + e % WPW] = pf[m];      \
         }                                                                               \
     } while (0)
-        KS_FETCH(0);
-        KS_STAGE(0);
+        KS_FETCH(ib);
+        KS_STAGE(ib & 1);
         __syncthreads();
-        for (int i = 0; i < kN; i++) {
-            if (i + 1 < kN) KS_FETCH(i + 1);
+        for (int i = ib; i < ie; i++) {
+            if (i + 1 < ie) KS_FETCH(i + 1);
             const uint32_t r = live ? (uint32_t)digc[(size_t)i * B] : 0u;
             consume(tab + (size_t)(i & 1) * TS, r);
-            if (i + 1 < kN) KS_STAGE((i + 1) & 1);
+            if (i + 1 < ie) KS_STAGE((i + 1) & 1);
             __syncthreads();
         }
 #undef KS_FETCH
@@ -176,28 +225,34 @@ __global__ __launch_bounds__(THREADS) void keyswitch_kernel(const T* __restrict_
             for (int m = 0; m < PMAX; m++)
                 if (lofs[m] >= 0) tab[(size_t)buf * P * TS + lofs[m]] = pf[m];
         };
-        fetch(0);
+        fetch(ib);
         stage(0);
         __syncthreads();
-        for (int i0 = 0, g = 0; i0 < kN; i0 += P, g++) {
+        for (int i0 = ib, g = 0; i0 < ie; i0 += P, g++) {
             // this group's coefficients first, so that waiting for them does
             // not wait for the next group's rows
             uint32_t rr[P];
 #pragma unroll
             for (int ii = 0; ii < P; ii++) rr[ii] = live ? (uint32_t)digc[(size_t)(i0 + ii) * B] : 0u;
-            if (i0 + P < kN) fetch(i0 + P);
+            if (i0 + P < ie) fetch(i0 + P);
             const T* tbuf = tab + (size_t)(g & 1) * P * TS;
 #pragma unroll
             for (int ii = 0; ii < P; ii++) consume(tbuf + ii * TS, rr[ii]);
-            if (i0 + P < kN) stage((g + 1) & 1);
+            if (i0 + P < ie) stage((g + 1) & 1);
             __syncthreads();
         }
     }
     if (!live) return;
     T* dst = out_ptrs ? (T*)(uintptr_t)out_ptrs[c] : out + (size_t)c * (n + 1);
+    if (!SPLIT) {
 #pragma unroll
-    for (int k = 0; k < WPW; k++)
-        if (w0 + k <= n) dst[w0 + k] = acc[k];
+        for (int k = 0; k < WPW; k++)
+            if (w0 + k <= n) dst[w0 + k] = acc[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < WPW; k++)
+            if (w0 + k <= n) atomicAdd(dst + w0 + k, acc[k]);
+    }
 }
 
 // ---- 32-bit words: the key switch as int8 matrix products.
@@ -217,7 +272,7 @@ __global__ __launch_bounds__(THREADS) void keyswitch_kernel(const T* __restrict_
 // fragment feeds KM_CT MFMAs; a wave's output tile holds 4 consecutive words
 // of one ciphertext per lane.
 
-template <int V, typename D, int TW, int KM_CT>
+template <int V, typename D, int TW, int KM_CT, bool SPLIT>
 __global__ __launch_bounds__(THREADS) void ks_mfma_kernel(const uint32_t* __restrict__ big, const D* __restrict__ dig,
                                                           const int8_t* __restrict__ ytab, uint32_t* out,
                                                           const uint64_t* out_ptrs, int B, int n, int kN, int t,
@@ -229,13 +284,14 @@ __global__ __launch_bounds__(THREADS) void ks_mfma_kernel(const uint32_t* __rest
     static_assert(CHU % THREADS == 0, "whole units per thread");
     __shared__ __attribute__((aligned(16))) int8_t tb[2][CHU * 16];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int z = (int)(blockIdx.x % 8) * pl.per + (int)(blockIdx.x / 8);
-    if (z >= pl.tiles * pl.groups) return;  // padding of the last run
-    const int tile = pl.tile_major ? z / pl.groups : z % pl.tiles;
-    const int grp = pl.tile_major ? z % pl.groups : z / pl.tiles;
+    int tile, grp, slice;
+    if (!ks_place<SPLIT>(pl, tile, grp, slice)) return;
     const int w0 = tile * TW * 16;
     const size_t K = (size_t)kN * t * V;
-    const int NCH = (int)(K / 64);
+    // this slice's chunks
+    const int cps = SPLIT ? ((int)(K / 64) + pl.slices - 1) / pl.slices : (int)(K / 64);
+    const int ch0 = SPLIT ? slice * cps : 0, NCH = SPLIT ? min(ch0 + cps, (int)(K / 64)) : (int)(K / 64);
+    if (SPLIT && ch0 >= NCH) return;
     const size_t plane = (size_t)Wp * K;  // bytes of one limb plane
     const int g = lane >> 4;
     const int cl = grp * 64 * KM_CT + wave * 16 * KM_CT + (lane & 15);  // this lane's ciphertext of tile 0 (tile ct: + 16 ct)
@@ -296,14 +352,14 @@ __global__ __launch_bounds__(THREADS) void ks_mfma_kernel(const uint32_t* __rest
 #pragma unroll
             for (int m = 0; m < 4; m++) acc[wt][ct][m] = v4i{0, 0, 0, 0};
 
-    fetch(0);
-    stage(0);
+    fetch(ch0);
+    stage(ch0 & 1);
     uint32_t dlo[KM_CT], dhi[KM_CT];
     int dj0 = 0;
 #pragma unroll
-    for (int ct = 0; ct < KM_CT; ct++) digit_rows(0, ct, dlo[ct], dhi[ct], dj0);
+    for (int ct = 0; ct < KM_CT; ct++) digit_rows(ch0, ct, dlo[ct], dhi[ct], dj0);
     __syncthreads();
-    for (int ch = 0; ch < NCH; ch++) {
+    for (int ch = ch0; ch < NCH; ch++) {
         const int buf = ch & 1;
         if (ch + 1 < NCH) fetch(ch + 1);
         v4i bx[KM_CT];
@@ -341,22 +397,27 @@ __global__ __launch_bounds__(THREADS) void ks_mfma_kernel(const uint32_t* __rest
                 uint32_t val = 0;
 #pragma unroll
                 for (int m = 0; m < 4; m++) val += (uint32_t)acc[wt][ct][m][e] << (8 * m);
-                dstp[w] = (w == n ? body : 0u) - val;
+                if (!SPLIT) dstp[w] = (w == n ? body : 0u) - val;
+                else atomicAdd(dstp + w, 0u - val);
             }
     }
 }
 
 template <int V, typename D, int TW, int KM_CT>
-int launch_mfma_ct(tfhe_ctx* c, const uint32_t* big, const D* dig, uint32_t* out, const uint64_t* out_ptrs,
+int launch_mfma_ct(tfhe_ctx* c, const uint32_t* big, D* dig, uint32_t* out, const uint64_t* out_ptrs,
                    uint32_t B, hipStream_t s) {
     const int n = (int)c->p.n, kN = (int)(c->p.k * c->p.N), t = (int)c->p.ks_t, bb = (int)c->p.ks_base_bits;
     KsPlace pl;
     pl.tiles = (c->ks_wp / 16 + TW - 1) / TW;
     pl.groups = (int)((B + 64 * KM_CT - 1) / (64 * KM_CT));
-    pl.per = (pl.tiles * pl.groups + 7) / 8;
+    pl.slices = ks_slices(c, pl.tiles * pl.groups, kN * t * V / 64, 4);
+    pl.per = (pl.tiles * pl.groups * pl.slices + 7) / 8;
+    hipLaunchKernelGGL((ks_digits_kernel<uint32_t, D>), dim3((kN + 63) / 64, (B + 63) / 64), dim3(THREADS), 0, s,
+                       big, dig, (int)B, kN, t * bb, n, out, out_ptrs, pl.slices > 1);
     const double table = 4.0 * c->ks_wp * kN * t * V, inputs = (double)B * kN * sizeof(D);
     pl.tile_major = table > inputs ? 1 : 0;
-    hipLaunchKernelGGL((ks_mfma_kernel<V, D, TW, KM_CT>), dim3(8 * pl.per), dim3(THREADS), 0, s, big, dig,
+    auto k = pl.slices > 1 ? ks_mfma_kernel<V, D, TW, KM_CT, true> : ks_mfma_kernel<V, D, TW, KM_CT, false>;
+    hipLaunchKernelGGL(k, dim3(8 * pl.per), dim3(THREADS), 0, s, big, (const D*)dig,
                        (const int8_t*)c->d_ksk8, out, out_ptrs, (int)B, n, kN, t, bb, c->ks_wp, pl);
     return hip_check(c, hipGetLastError(), "launch ks_mfma");
 }
@@ -364,10 +425,7 @@ int launch_mfma_ct(tfhe_ctx* c, const uint32_t* big, const D* dig, uint32_t* out
 template <int V, typename D, int TW>
 int launch_mfma_ks(tfhe_ctx* c, const uint32_t* big, void* dig_ws, uint32_t* out, const uint64_t* out_ptrs,
                    uint32_t B, hipStream_t s) {
-    const int kN = (int)(c->p.k * c->p.N), t = (int)c->p.ks_t, bb = (int)c->p.ks_base_bits;
     D* dig = (D*)dig_ws;
-    hipLaunchKernelGGL((ks_digits_kernel<uint32_t, D>), dim3((kN + 63) / 64, (B + 63) / 64), dim3(THREADS), 0, s,
-                       big, dig, (int)B, kN, t * bb);
     // 4 ciphertext tiles per wave, or 2 when that leaves CUs idle (measured:
     // 4096 ciphertexts at n = 64 0.069 -> 0.052 ms; 4 is faster once the grid
     // fills the chip)
@@ -383,15 +441,16 @@ int launch_p(tfhe_ctx* c, const T* big, void* dig_ws, T* out, const uint64_t* ou
     constexpr int RS = WPW + Vec16<T>::N;
     const size_t lds = 2ull * P * t * V * RS * sizeof(T);
     D* dig = (D*)dig_ws;
-    hipLaunchKernelGGL((ks_digits_kernel<T, D>), dim3((kN + 63) / 64, (B + 63) / 64), dim3(THREADS), 0, s, big, dig,
-                       (int)B, kN, t * bb);
-    auto k = keyswitch_kernel<T, D, V, WPW, P>;
-    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return hip_check(c, e, "hipFuncSetAttribute(keyswitch)");
     KsPlace pl;
     pl.tiles = (n + 1 + WPW - 1) / WPW;
     pl.groups = (int)((B + TC - 1) / TC);
-    pl.per = (pl.tiles * pl.groups + 7) / 8;
+    pl.slices = ks_slices(c, pl.tiles * pl.groups, kN / P, 8);
+    pl.per = (pl.tiles * pl.groups * pl.slices + 7) / 8;
+    auto k = pl.slices > 1 ? keyswitch_kernel<T, D, V, WPW, P, true> : keyswitch_kernel<T, D, V, WPW, P, false>;
+    hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return hip_check(c, e, "hipFuncSetAttribute(keyswitch)");
+    hipLaunchKernelGGL((ks_digits_kernel<T, D>), dim3((kN + 63) / 64, (B + 63) / 64), dim3(THREADS), 0, s, big, dig,
+                       (int)B, kN, t * bb, n, out, out_ptrs, pl.slices > 1);
     const double table = (double)kN * t * V * (n + 1), inputs = (double)B * (kN + 1);
     pl.tile_major = table > inputs ? 1 : 0;
     hipLaunchKernelGGL(k, dim3(8 * pl.per), dim3(THREADS), lds, s, big, (const D*)dig, (const T*)c->d_ksk, out,
