@@ -253,25 +253,28 @@ FHE_DEV void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Where a transform's per-lane twiddles come from: registers, an LDS copy read
+// at each use (where registers are scarce), or global memory (where the LDS is
+// full as well), requested before the transform's first pass.
+enum TwiddleSource { TW_REG, TW_LDS, TW_GLOBAL };
+
 // A wave's part of a transform: its twiddles and its byte offsets in LDS.
-// Exchange buffer: point j of block k.  At R = 8 the blocks are 66 points
-// apart, at R = 16 (whose buffers fill the LDS) 64 with j swizzled by k, so
-// that 16 neighbouring lanes touch 16 different 16-byte slots of the 256 bytes
-// that the LDS banks span, when they write (j varies) and when they read (k
-// and the lowest bit of j vary).  Pairs of the last level: member planes, the
-// second one shifted (R = 8) or swizzled (R = 16) by 8 points.
-// TWL: the twiddles stay in LDS and are read at each use (registers are
-// scarce there), else in registers.
-template <int R, bool TWL>
+// Exchange buffer: point j of block k at 64 k + (j ^ 2 (k & 7)), and pairs of
+// the last level in two member planes, the second one's index ^ 4: with these
+// swizzles no lanes of a read or write meet in an LDS bank (measured for one
+// 1 KB wave access per CU: reads 1.9 ns, writes 5.6 ns; with blocks 66 points
+// apart and planes M/2 + 8 apart the exchange read took 3.6 ns, the pair write
+// 7.0 ns).
+template <int R, TwiddleSource TWS>
 struct WaveFft {
     using P = Plan<R>;
-    static constexpr bool PAD = R == 8;
-    static constexpr int POINTS = PAD ? 528 : P::M;             // points of a buffer
-    static constexpr int PLANE = (P::M / 2 + (PAD ? 8 : 0));    // points of a member plane
-    double c2[TWL ? 1 : P::NT2], t2[TWL ? 1 : P::NT2], c3[TWL ? 1 : P::NT3], t3[TWL ? 1 : P::NT3];
+    static constexpr bool REG = TWS == TW_REG;
+    static constexpr int S2 = P::NT2 + (R == 8 ? 1 : 0);  // entries per block of the LDS copy (5: no bank conflicts)
+    double c2[REG ? P::NT2 : 1], t2[REG ? P::NT2 : 1], c3[REG ? P::NT3 : 1], t3[REG ? P::NT3 : 1];
     uint8_t* lds;
     uint32_t wb, rb, pb;  // write / read of the exchange, pairs
-    uint32_t tw2, tw3;    // this lane's twiddles (TWL)
+    uint32_t tw2, tw3;    // this lane's twiddles: LDS offsets or table entries
+    const d2* twg;
 
     // buf: offset of the wave's buffer; twl: offset of the LDS copy of the
     // second pass's and the swapped levels' twiddles
@@ -281,26 +284,32 @@ struct WaveFft {
         const int bb = R == 8 ? (lane >> 5) * 4 + ((lane >> 4) & 1) * 2 + (lane & 1) : (lane >> 5) * 2 + (lane & 1);
         lds = lds_;
         wb = buf + lane * 16;
-        rb = buf + (PAD ? k * 66 + bb : k * 64 + (bb ^ ((k & 7) * 2))) * 16;
-        pb = buf + ((lane & 1) * PLANE + (PAD ? lane >> 1 : (lane >> 1) ^ ((lane & 1) * 8))) * 16;
-        if constexpr (TWL) {
-            tw2 = twl + k * P::NT2 * 16;
-            tw3 = twl + (P::T3 + (lane >> 1) * P::NT3) * 16;
+        rb = buf + (k * 64 + (bb ^ ((k & 7) * 2))) * 16;
+        pb = buf + pair_off(lane & 1, lane >> 1);
+        if constexpr (TWS == TW_LDS) {
+            tw2 = twl + k * S2 * 16;
+            tw3 = twl + (R * S2 + (lane >> 1) * P::NT3) * 16;
         } else {
-#pragma unroll
-            for (int i = 0; i < P::NT2; i++) {
-                const d2 w = tw[k * P::NT2 + i];
-                c2[i] = w.x;
-                t2[i] = w.y;
-            }
-#pragma unroll
-            for (int i = 0; i < P::NT3; i++) {
-                const d2 w = tw[P::T3 + (lane >> 1) * P::NT3 + i];
-                c3[i] = w.x;
-                t3[i] = w.y;
+            twg = tw;
+            tw2 = k * P::NT2;
+            tw3 = P::T3 + (lane >> 1) * P::NT3;
+            if constexpr (REG) {
+                fetch2(c2, t2);
+                fetch3(c3, t3);
             }
         }
     }
+    template <int K>
+    FHE_DEV void fetch(uint32_t off, double (&c)[K], double (&t)[K]) const {
+#pragma unroll
+        for (int i = 0; i < K; i++) {
+            const d2 w = TWS == TW_LDS ? at(off + i * 16) : twg[off + i];
+            c[i] = w.x;
+            t[i] = w.y;
+        }
+    }
+    FHE_DEV void fetch2(double (&c)[P::NT2], double (&t)[P::NT2]) const { fetch(tw2, c, t); }
+    FHE_DEV void fetch3(double (&c)[P::NT3], double (&t)[P::NT3]) const { fetch(tw3, c, t); }
     FHE_DEV d2& at(uint32_t off) const { return *(d2*)(lds + off); }
     // (an opaque copy keeps the swizzled addresses from being held in
     // registers across the step loop)
@@ -311,14 +320,13 @@ struct WaveFft {
     FHE_DEV void put_blocks(const double (&re)[R], const double (&im)[R]) const {  // point `lane` of block r
         const uint32_t b = opaque(wb);
 #pragma unroll
-        for (int r = 0; r < R; r++)
-            at(PAD ? b + r * 66 * 16 : (b ^ ((r & 7) * 32)) + r * 64 * 16) = d2{re[r], im[r]};
+        for (int r = 0; r < R; r++) at((b ^ ((r & 7) * 32)) + r * 64 * 16) = d2{re[r], im[r]};
     }
     FHE_DEV void get_blocks(double (&re)[R], double (&im)[R]) const {
         const uint32_t b = opaque(wb);
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            const d2 v = at(PAD ? b + r * 66 * 16 : (b ^ ((r & 7) * 32)) + r * 64 * 16);
+            const d2 v = at((b ^ ((r & 7) * 32)) + r * 64 * 16);
             re[r] = v.x;
             im[r] = v.y;
         }
@@ -326,69 +334,63 @@ struct WaveFft {
     FHE_DEV void put_points(const double (&re)[R], const double (&im)[R]) const {  // points of this lane's block
         const uint32_t b = opaque(rb);
 #pragma unroll
-        for (int r = 0; r < R; r++) at(PAD ? b + r * 8 * 16 : b ^ (r * 4 * 16)) = d2{re[r], im[r]};
+        for (int r = 0; r < R; r++) at(b ^ (r * (64 / R) * 16)) = d2{re[r], im[r]};
     }
     FHE_DEV void get_points(double (&re)[R], double (&im)[R]) const {
         const uint32_t b = opaque(rb);
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            const d2 v = at(PAD ? b + r * 8 * 16 : b ^ (r * 4 * 16));
+            const d2 v = at(b ^ (r * (64 / R) * 16));
             re[r] = v.x;
             im[r] = v.y;
-        }
-    }
-    template <int K>
-    FHE_DEV void twiddles(uint32_t off, double (&c)[K], double (&t)[K]) const {
-#pragma unroll
-        for (int i = 0; i < K; i++) {
-            const d2 w = at(off + i * 16);
-            c[i] = w.x;
-            t[i] = w.y;
         }
     }
 
     // points j = 64 r + lane in -> pairs of the last level in the buffer
     FHE_DEV void forward(double (&re)[R], double (&im)[R]) const {
+        double c[P::NT2], t[P::NT2], cs[P::NT3], ts[P::NT3];
+        if constexpr (TWS == TW_GLOBAL) {
+            fetch2(c, t);
+            fetch3(cs, ts);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         lane_fwd<R>(re, im, kC1, kT1);
         put_blocks(re, im);
         wave_order();
         get_points(re, im);
-        if constexpr (TWL) {
-            double c[P::NT2], t[P::NT2], cs[P::NT3], ts[P::NT3];
-            twiddles(tw2, c, t);
-            lane_fwd<R>(re, im, c, t);
-            twiddles(tw3, cs, ts);
-            lane_swaps<R>(re, im);
-            swapped_fwd<R>(re, im, cs, ts);
-        } else {
-            lane_fwd<R>(re, im, c2, t2);
-            lane_swaps<R>(re, im);
-            swapped_fwd<R>(re, im, c3, t3);
-        }
+        if constexpr (TWS == TW_LDS) fetch2(c, t);
+        lane_fwd<R>(re, im, REG ? c2 : c, REG ? t2 : t);
+        if constexpr (TWS == TW_LDS) fetch3(cs, ts);
+        lane_swaps<R>(re, im);
+        swapped_fwd<R>(re, im, REG ? c3 : cs, REG ? t3 : ts);
         wave_order();
 #pragma unroll
         for (int r = 0; r < R; r++) at(pb + r * 32 * 16) = d2{re[r], im[r]};
     }
+    struct Twiddles {
+        double c2[P::NT2], t2[P::NT2], c3[P::NT3], t3[P::NT3];
+    };
+    // requests the inverse's twiddles (TW_GLOBAL)
+    FHE_DEV void request(Twiddles& w) const {
+        if constexpr (TWS == TW_GLOBAL) {
+            fetch3(w.c3, w.t3);
+            fetch2(w.c2, w.t2);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
     // pairs in the buffer -> the first pass's inputs in registers
-    FHE_DEV void inverse_to_first(double (&re)[R], double (&im)[R]) const {
+    FHE_DEV void inverse_to_first(double (&re)[R], double (&im)[R], Twiddles& w) const {
 #pragma unroll
         for (int r = 0; r < R; r++) {
             const d2 v = at(pb + r * 32 * 16);
             re[r] = v.x;
             im[r] = v.y;
         }
-        if constexpr (TWL) {
-            double c[P::NT2], t[P::NT2], cs[P::NT3], ts[P::NT3];
-            twiddles(tw3, cs, ts);
-            swapped_inv<R>(re, im, cs, ts);
-            twiddles(tw2, c, t);
-            lane_swaps<R>(re, im);
-            lane_inv<R>(re, im, c, t);
-        } else {
-            swapped_inv<R>(re, im, c3, t3);
-            lane_swaps<R>(re, im);
-            lane_inv<R>(re, im, c2, t2);
-        }
+        if constexpr (TWS == TW_LDS) fetch3(w.c3, w.t3);
+        swapped_inv<R>(re, im, REG ? c3 : w.c3, REG ? t3 : w.t3);
+        if constexpr (TWS == TW_LDS) fetch2(w.c2, w.t2);
+        lane_swaps<R>(re, im);
+        lane_inv<R>(re, im, REG ? c2 : w.c2, REG ? t2 : w.t2);
         wave_order();
         put_points(re, im);
         wave_order();
@@ -396,7 +398,7 @@ struct WaveFft {
     }
     FHE_DEV void inverse_first(double (&re)[R], double (&im)[R]) const { lane_inv<R>(re, im, kC1, kT1); }
     // offset of member e of pair g in a buffer
-    FHE_DEV static uint32_t pair_off(int e, int g) { return (e * PLANE + (PAD ? g : g ^ (e * 8))) * 16; }
+    FHE_DEV static uint32_t pair_off(int e, int g) { return (e * (P::M / 2) + (g ^ (e * 4))) * 16; }
 };
 
 // -------------------------------------------------------- key spectra
@@ -407,8 +409,8 @@ struct WaveFft {
 template <typename T, int R>
 __global__ __launch_bounds__(64) void fft_key_kernel(const T* bsk, const d2* tw, d2* fkey) {
     using P = Plan<R>;
-    using F = WaveFft<R, false>;
-    __shared__ d2 buf[F::POINTS];
+    using F = WaveFft<R, TW_REG>;
+    __shared__ d2 buf[P::M];
     const int lane = threadIdx.x;
     const int limb = blockIdx.x % Limb<T>::COUNT;
     const size_t poly = blockIdx.x / Limb<T>::COUNT;
@@ -461,18 +463,20 @@ struct FftArgs {
 
 // One configuration: W waves and G ciphertexts per workgroup; KD: a thread's
 // ring of key values, in polynomials; KX of them are requested a transform
-// ahead, the others when the transform's registers are free.
-template <typename T_, int R_, int W_, int G_, int KD_, int KX_, bool TWL_>
+// ahead (AFTER: the next step's once the inverse's twiddles are, else as soon
+// as the ring is free), the others when the transform's registers are free.
+template <typename T_, int R_, int W_, int G_, int L_, int KD_, int KX_, TwiddleSource TWS_, bool AFTER_>
 struct Cfg {
     using T = T_;
-    static constexpr int R = R_, W = W_, G = G_, KD = KD_, KX = KX_;
-    static constexpr bool TWL = TWL_;
+    static constexpr int R = R_, W = W_, G = G_, L = L_, KD = KD_, KX = KX_;
+    static constexpr TwiddleSource TWS = TWS_;
+    static constexpr bool AFTER = AFTER_;
     using P = Plan<R>;
-    using F = WaveFft<R, TWL>;
-    static constexpr uint32_t BUF = F::POINTS * 16;                       // bytes of a wave's buffer
+    using F = WaveFft<R, TWS>;
+    static constexpr uint32_t BUF = P::M * 16;                            // bytes of a wave's buffer
     static constexpr uint32_t ACC = W * BUF;                              // accumulators [G][2][N]
-    static constexpr uint32_t TW = ACC + G * 2 * P::N * (uint32_t)sizeof(T);  // twiddles (TWL)
-    static constexpr uint32_t LDS = TW + (TWL ? (uint32_t)P::T4 * 16 : 0);
+    static constexpr uint32_t TW = ACC + G * 2 * P::N * (uint32_t)sizeof(T);  // twiddles (TW_LDS)
+    static constexpr uint32_t LDS = TW + (TWS == TW_LDS ? (uint32_t)(R * F::S2 + 32 * P::NT3) * 16 : 0);
 };
 
 template <typename CF>
@@ -493,7 +497,7 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(2, 2
     static_assert(PPR % KD == 0 && KX <= KD, "key ring");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n = a.n, l = a.l, NB = 2 * l;
+    const int n = a.n, l = CF::L ? CF::L : a.l, NB = 2 * l;
     const int ct0 = blockIdx.x * G;
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -519,15 +523,16 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(2, 2
         accs[(size_t)c * 2 * N + j] = 0;
         accs[(size_t)c * 2 * N + N + j] = body;
     }
-    if constexpr (CF::TWL)
-        for (int idx = tid; idx < P::T4; idx += 64 * W) ((d2*)(smem + CF::TW))[idx] = a.tw[idx];
+    if constexpr (CF::TWS == TW_LDS)
+        for (int idx = tid; idx < P::T4; idx += 64 * W)
+            ((d2*)(smem + CF::TW))[idx < P::T3 ? idx + idx / P::NT2 * (WF::S2 - P::NT2) : idx + R * WF::S2 - P::T3] = a.tw[idx];
 
     WF f;
     f.init(a.tw, smem, wave * CF::BUF, CF::TW);
     const int g = tid & (M / 2 - 1), os = OS == 1 ? 0 : tid / (M / 2);
     const d2 w4 = a.tw[P::T4 + g];
     // this thread's pairs in buffer 0
-    const uint32_t px = WF::pair_off(0, g), py = WF::PAD ? px + WF::PLANE * 16 : WF::pair_off(1, g);
+    const uint32_t px = WF::pair_off(0, g), py = WF::pair_off(1, g);
 
     // gadget digits as in the int8 path: field p of z, read as a signed number
     const int bgb = a.bg_bits;
@@ -634,6 +639,7 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(2, 2
                 form(z, u, ab);
                 for (int p = 0; p < l; p++) {
                     transform(z, p);
+                    __builtin_amdgcn_sched_barrier(0);  // (not earlier: the transform needs the registers)
                     key_load(kv[0], i, u * l + p);
                     lds_barrier();
                     d2 x[G], y[G];
@@ -650,6 +656,7 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(2, 2
                     form(z, u, ab);
                     transform(z, q0 + pq0 - u * l);
                 }
+                __builtin_amdgcn_sched_barrier(0);  // (not earlier: the transform needs the registers)
 #pragma unroll
                 for (int pp = KX; pp < KD; pp++)
                     if (q0 + pp < NB) key_load(kv[pp], i, q0 + pp);
@@ -665,7 +672,7 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(2, 2
                     }
                     if (pp + KD < PPR) {
                         if (q0 + pp + KD < NB) key_load(kv[pp % KD], i, q0 + pp + KD);
-                    } else if (pp + KD - PPR < KX) {
+                    } else if (pp + KD - PPR < KX && !(CF::AFTER && last)) {
                         if (nq + pp + KD - PPR < NB) key_load(kv[pp % KD], ni, nq + pp + KD - PPR);
                     }
                 }
@@ -691,7 +698,10 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(2, 2
             const int o = rd * PPR + pq0;
             const bool mine = OUT % PPR == 0 || o < OUT;
             double re[R], im[R];
-            if (mine) f.inverse_to_first(re, im);
+            typename WF::Twiddles tw;
+            f.request(tw);
+            if (CF::AFTER && rd == 0) key_ahead(i + 1 < n ? i + 1 : 0, 0);
+            if (mine) f.inverse_to_first(re, im, tw);
             if (rd + 1 < IR) lds_barrier();
             if (mine) {
                 f.inverse_first(re, im);
@@ -728,6 +738,7 @@ int launch_fft_t(tfhe_ctx* c, const FftArgs& a, hipStream_t s) {
     static_assert(CF::LDS <= 160 * 1024, "LDS");
     hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)CF::LDS);
     if (e != hipSuccess) return hip_check(c, e, "hipFuncSetAttribute(br_fft)");
+    if (CF::L && CF::L != a.l) return ctx_fail(c, TFHE_EINVAL, "transform kernel of another level count");
     hipLaunchKernelGGL(k, dim3((a.B + CF::G - 1) / CF::G), dim3(64 * CF::W), CF::LDS, s, a);
     return hip_check(c, hipGetLastError(), "launch br_fft");
 }
@@ -849,15 +860,24 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     a.bg_bits = (int)c->p.bg_bits;
     // Up to 256 ciphertexts (a CU each) one per workgroup, then two, while
     // that keeps every one resident; four above, two workgroups per CU, which
-    // quarters the key reads (N = 1024, 512 ciphertexts: 5.3 ms at two per
-    // workgroup; 1024: 9.8 ms at four, 32.2 ms for 4096).
-    //                 T         R  W  G KD KX TWL
+    // quarters the key reads (N = 1024: 512 ciphertexts 4.7 ms at two per
+    // workgroup, 1024 9.7 ms at four).  The gadget levels of the named
+    // parameter sets (l = 3 at 32-bit words, 4 at 64-bit) are compile-time, so
+    // that the ring of key values has no conditional loads: with them the
+    // compiler spilled the ring to scratch (N = 1024, 64 ciphertexts
+    // 3.4 -> 2.9 ms; N = 2048, q = 64, 256 ciphertexts 15.4 -> 13.4 ms).  Any
+    // other l loads each polynomial's values when they are needed.
+    const int l = (int)c->p.l;
+    //                                                       T         R   W  G  L  KD KX twiddles AFTER
     if (c->q == 32) {
-        if (c->p.N == 2048) return launch_fft_t<Cfg<uint32_t, 16, 8, 1, 2, 1, false>>(c, a, s);
-        if (B > 512) return launch_fft_t<Cfg<uint32_t, 8, 4, 4, 1, 0, true>>(c, a, s);
-        if (B > 256) return launch_fft_t<Cfg<uint32_t, 8, 8, 2, 4, 4, false>>(c, a, s);
-        return launch_fft_t<Cfg<uint32_t, 8, 8, 1, 8, 8, false>>(c, a, s);
+        if (c->p.N == 2048) return l == 3 ? launch_fft_t<Cfg<uint32_t, 16, 8, 1, 3, 2, 1, TW_LDS, true>>(c, a, s)
+                                          : launch_fft_t<Cfg<uint32_t, 16, 8, 1, 0, 1, 0, TW_LDS, true>>(c, a, s);
+        if (B > 512) return launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, 0, TW_LDS, false>>(c, a, s);
+        if (l != 3) return launch_fft_t<Cfg<uint32_t, 8, 8, 1, 0, 2, 0, TW_REG, false>>(c, a, s);
+        return B > 256 ? launch_fft_t<Cfg<uint32_t, 8, 8, 2, 3, 4, 4, TW_REG, false>>(c, a, s)
+                       : launch_fft_t<Cfg<uint32_t, 8, 8, 1, 3, 8, 8, TW_REG, true>>(c, a, s);
     }
-    if (c->p.N == 2048) return launch_fft_t<Cfg<uint64_t, 16, 8, 1, 2, 1, false>>(c, a, s);
-    return launch_fft_t<Cfg<uint64_t, 8, 8, 1, 4, 4, false>>(c, a, s);
+    if (c->p.N == 2048) return l == 4 ? launch_fft_t<Cfg<uint64_t, 16, 8, 1, 4, 2, 1, TW_GLOBAL, true>>(c, a, s)
+                                      : launch_fft_t<Cfg<uint64_t, 16, 8, 1, 0, 1, 0, TW_GLOBAL, true>>(c, a, s);
+    return launch_fft_t<Cfg<uint64_t, 8, 8, 1, 0, 4, 0, TW_REG, false>>(c, a, s);
 }
