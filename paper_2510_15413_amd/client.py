@@ -13,10 +13,8 @@ def bit_mu(p, bits: torch.Tensor) -> torch.Tensor:
     """Gate encoding (2b - 1)/8 of a tensor of bits, as torus words."""
     e = 1 << (p.q - 3)
     dt = _lib.torch_dtype(p.q)
-    bits = bits.to(device="cuda", dtype=torch.int64)
-    mu = torch.where(bits != 0, torch.tensor(e, dtype=torch.int64, device="cuda"),
-                     torch.tensor(-e, dtype=torch.int64, device="cuda"))
-    return mu.to(dt) if p.q == 32 else mu
+    # (Python scalars: device scalars would be copied from the host, a wait each)
+    return (bits.to(device="cuda", dtype=torch.int64) != 0).to(dt) * (2 * e) - e
 
 
 def value_bits(values: torch.Tensor, w: int) -> torch.Tensor:
