@@ -62,7 +62,9 @@ struct Vec16<uint64_t> {
 // Rounded digits of a 64 x 64 block (ciphertexts x coefficients): rows of
 // the ciphertexts are read coalesced, turned in LDS, and written as rows of
 // the coefficient-major digit array.
-template <typename T, typename D>
+// VEC: eight coefficients of a ciphertext together, [i/8][c][8] (16-bit digits,
+// kN a multiple of 64), else [i][c].
+template <typename T, typename D, bool VEC = false>
 __global__ __launch_bounds__(THREADS) void ks_digits_kernel(const T* __restrict__ big, D* __restrict__ dig, int B,
                                                             int kN, int tb, int n, T* out, const uint64_t* out_ptrs,
                                                             int set_out) {
@@ -84,10 +86,22 @@ __global__ __launch_bounds__(THREADS) void ks_digits_kernel(const T* __restrict_
         blk[r][lane] = (c < B && i < kN) ? (uint32_t)round_top<T>(big[(size_t)c * (kN + 1) + i], tb) : 0u;
     }
     __syncthreads();
+    if constexpr (VEC) {
+        static_assert(sizeof(D) == 2, "16-bit digits");
 #pragma unroll
-    for (int m = 0; m < 16; m++) {
-        const int col = w + 4 * m, c = c0 + lane, i = i0 + col;
-        if (c < B && i < kN) dig[(size_t)i * B + c] = (D)blk[lane][col];
+        for (int m = 0; m < 2; m++) {
+            const int v = w + 4 * m, c = c0 + lane;  // coefficients i0 + 8 v ..
+            const uint32_t* x = &blk[lane][8 * v];
+            if (c < B)
+                ((uint4*)dig)[(size_t)(i0 / 8 + v) * B + c] =
+                    make_uint4(x[0] | x[1] << 16, x[2] | x[3] << 16, x[4] | x[5] << 16, x[6] | x[7] << 16);
+        }
+    } else {
+#pragma unroll
+        for (int m = 0; m < 16; m++) {
+            const int col = w + 4 * m, c = c0 + lane, i = i0 + col;
+            if (c < B && i < kN) dig[(size_t)i * B + c] = (D)blk[lane][col];
+        }
     }
 }
 
@@ -107,9 +121,10 @@ struct KsPlace {
 // 45 -> 14 us; n = 750, N = 2048 (q = 64) 1 ciphertext 3270 -> 290 us, 40
 // 3273 -> 341 us, 1000 3330 -> 1295 us.  Two per CU: 37, 52, 104, 14, 378, 393,
 // 1868 us.
-int ks_slices(const tfhe_ctx* c, int wgs, int steps, int per_cu) {
+// `full`: workgroups per CU from which on one slice is as good.
+int ks_slices(const tfhe_ctx* c, int wgs, int steps, int per_cu, int full = 1) {
     const int cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
-    if (wgs >= cus) return 1;
+    if (wgs >= full * cus) return 1;
     return std::max(1, std::min(per_cu * cus / wgs, steps / 8));
 }
 
@@ -403,6 +418,158 @@ __global__ __launch_bounds__(THREADS) void ks_mfma_kernel(const uint32_t* __rest
     }
 }
 
+// The same product for b = 2, t = 8 (the standard set): a coefficient's digits
+// are 16 bits, so a lane's 16 bytes of a 64-k chunk are the four digits of one
+// byte of a digit word, at a place that depends on the lane alone, and byte d of
+// word p is set by one shift.  The generic form above spends about ten vector
+// operations per digit finding its place and waits for the table at every
+// chunk; here four chunks (eight coefficients, one 16-byte digit vector per
+// ciphertext) are staged per barrier, so that a table read has 64 MFMAs to
+// arrive.  The table's 16-byte units lie in LDS as the lanes read them,
+// swizzled by (chunk, part) so that the 16 lanes that write one word's units
+// touch 16 slots.  Bounded by the matrix pipe and the digit words (52 vector
+// operations beside 16 MFMAs of 16 cycles).  Measured at n = 630, N = 1024, the
+// generic form -> this: 1 ciphertext 32 -> 25 us, 300 92 -> 63 us, 1024
+// 319 -> 111 us, 2048 451 -> 200 us, 4096 568 -> 322 us, 65,536 6.68 -> 4.55 ms.
+template <int KM_CT, bool SPLIT>
+__global__ __launch_bounds__(THREADS) void ks_mfma8_kernel(const uint32_t* __restrict__ big,
+                                                           const uint4* __restrict__ dig8v,
+                                                           const int8_t* __restrict__ ytab, uint32_t* out,
+                                                           const uint64_t* out_ptrs, int B, int n, int kN, int Wp,
+                                                           KsPlace pl) {
+    typedef int v4i __attribute__((ext_vector_type(4)));
+    typedef uint32_t w4 __attribute__((ext_vector_type(4)));  // (held as HIP's uint4 the prefetch went through scratch)
+    constexpr int SC = 4;                   // chunks per stage
+    constexpr int UNITS = SC * 4 * 64;      // 16-byte units of table per stage: chunks x limbs x (4 parts x 16 words)
+    constexpr int UPT = UNITS / THREADS;    // = 4, one per limb
+    __shared__ __attribute__((aligned(16))) w4 tb[2][UNITS];
+    const w4* dig8 = (const w4*)dig8v;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    int tile, grp, slice;
+    if (!ks_place<SPLIT>(pl, tile, grp, slice)) return;
+    const int w0 = tile * 16;
+    const size_t K = (size_t)kN * 32;
+    const size_t plane = (size_t)Wp * K;  // bytes of one limb plane
+    const int NST = kN / 8;               // stages
+    const int sps = SPLIT ? (NST + pl.slices - 1) / pl.slices : NST;
+    const int s0 = SPLIT ? slice * sps : 0, s1 = SPLIT ? min(s0 + sps, NST) : NST;
+    if (SPLIT && s0 >= s1) return;
+    const int g = lane >> 4, r = lane & 15;
+    const int cl = grp * 64 * KM_CT + wave * 16 * KM_CT + r;  // this lane's ciphertext of tile 0
+
+    // thread: word tid/16 of every limb, 16 bytes part tid%16 of the stage's 256
+    const int word = tid >> 4, part = tid & 15;
+    const int8_t* src = ytab + (size_t)(w0 + word) * K + 16 * part;
+    const int dst = (part >> 2) * 256 + (part & 3) * 16 + (word ^ part);  // + 64 limb
+    w4 st[UPT];
+    auto fetch = [&](int s) {
+#pragma unroll
+        for (int m = 0; m < UPT; m++) st[m] = *(const w4*)(src + (size_t)m * plane + (size_t)s * 256);
+    };
+    auto stage = [&](int buf) {
+#pragma unroll
+        for (int m = 0; m < UPT; m++) tb[buf][dst + 64 * m] = st[m];
+    };
+    w4 dv[KM_CT];
+    auto digits = [&](int s) {
+#pragma unroll
+        for (int ct = 0; ct < KM_CT; ct++) dv[ct] = dig8[(size_t)s * B + min(cl + 16 * ct, B - 1)];
+    };
+    // the lane's digits are byte 2 (g/2) + 1 - g%2 of a chunk's 32 digit bits
+    const int sh = 8 * (2 * (g >> 1) + 1 - (g & 1));
+    auto onehot = [&](uint32_t w) -> v4i {
+        const uint32_t x = w >> sh;
+        v4i o;
+#pragma unroll
+        for (int p = 0; p < 4; p++) o[p] = (int)(1u << (8 * ((x >> (6 - 2 * p)) & 3)));
+        return o;
+    };
+
+    v4i acc[KM_CT][4];
+#pragma unroll
+    for (int ct = 0; ct < KM_CT; ct++)
+#pragma unroll
+        for (int m = 0; m < 4; m++) acc[ct][m] = v4i{0, 0, 0, 0};
+
+    fetch(s0);
+    digits(s0);
+    stage(0);
+    __syncthreads();
+    for (int s = s0; s < s1; s++) {
+        const int buf = (s - s0) & 1;
+        w4 cur[KM_CT];
+#pragma unroll
+        for (int ct = 0; ct < KM_CT; ct++) cur[ct] = dv[ct];
+        if (s + 1 < s1) {
+            fetch(s + 1);
+            digits(s + 1);
+        }
+#pragma unroll
+        for (int ch = 0; ch < SC; ch++) {
+            v4i bx[KM_CT];
+#pragma unroll
+            for (int ct = 0; ct < KM_CT; ct++)
+                bx[ct] = onehot(cur[ct][ch]);
+#pragma unroll
+            for (int m = 0; m < 4; m++) {
+                const v4i av = *(const v4i*)&tb[buf][(ch * 4 + m) * 64 + g * 16 + (r ^ (ch * 4 + g))];
+#pragma unroll
+                for (int ct = 0; ct < KM_CT; ct++)
+                    acc[ct][m] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av, bx[ct], acc[ct][m], 0, 0, 0);
+            }
+        }
+        if (s + 1 < s1) stage(buf ^ 1);
+        __syncthreads();
+    }
+    // lane holds words w0 + 4g + e of ciphertext cl + 16 ct
+#pragma unroll
+    for (int ct = 0; ct < KM_CT; ct++) {
+        const int c = cl + 16 * ct;
+        if (c >= B) continue;
+        uint32_t* dstp = out_ptrs ? (uint32_t*)(uintptr_t)out_ptrs[c] : out + (size_t)c * (n + 1);
+        const uint32_t body = big[(size_t)c * (kN + 1) + kN];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const int w = w0 + 4 * g + e;
+            if (w > n) continue;
+            uint32_t val = 0;
+#pragma unroll
+            for (int m = 0; m < 4; m++) val += (uint32_t)acc[ct][m][e] << (8 * m);
+            if (!SPLIT) dstp[w] = (w == n ? body : 0u) - val;
+            else atomicAdd(dstp + w, 0u - val);
+        }
+    }
+}
+
+template <int KM_CT>
+int launch_mfma8_ct(tfhe_ctx* c, const uint32_t* big, void* dig, uint32_t* out, const uint64_t* out_ptrs, uint32_t B,
+                    hipStream_t s) {
+    const int n = (int)c->p.n, kN = (int)(c->p.k * c->p.N);
+    KsPlace pl;
+    pl.tiles = c->ks_wp / 16;
+    pl.groups = (int)((B + 64 * KM_CT - 1) / (64 * KM_CT));
+    pl.slices = ks_slices(c, pl.tiles * pl.groups, kN / 8, 4, 2);
+    pl.per = (pl.tiles * pl.groups * pl.slices + 7) / 8;
+    const double table = 4.0 * c->ks_wp * kN * 32, inputs = 2.0 * B * kN;
+    pl.tile_major = table > inputs ? 1 : 0;
+    hipLaunchKernelGGL((ks_digits_kernel<uint32_t, uint16_t, true>), dim3(kN / 64, (B + 63) / 64), dim3(THREADS), 0, s,
+                       big, (uint16_t*)dig, (int)B, kN, 16, n, out, out_ptrs, pl.slices > 1);
+    auto k = pl.slices > 1 ? ks_mfma8_kernel<KM_CT, true> : ks_mfma8_kernel<KM_CT, false>;
+    hipLaunchKernelGGL(k, dim3(8 * pl.per), dim3(THREADS), 0, s, big, (const uint4*)dig, (const int8_t*)c->d_ksk8, out,
+                       out_ptrs, (int)B, n, kN, c->ks_wp, pl);
+    return hip_check(c, hipGetLastError(), "launch ks_mfma8");
+}
+
+int launch_mfma8(tfhe_ctx* c, const uint32_t* big, void* dig, uint32_t* out, const uint64_t* out_ptrs, uint32_t B,
+                 hipStream_t s) {
+    const int cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
+    const int64_t wgs4 = (int64_t)(c->ks_wp / 16) * ((B + 255) / 256);
+    // 2 ciphertext tiles per wave until 4 fill the CUs twice over (2048
+    // ciphertexts: 200 us at 2, 245 us at 4; 4096 326 us at 4, 470 us at 2)
+    if (wgs4 < 2 * cus) return launch_mfma8_ct<2>(c, big, dig, out, out_ptrs, B, s);
+    return launch_mfma8_ct<4>(c, big, dig, out, out_ptrs, B, s);
+}
+
 template <int V, typename D, int TW, int KM_CT>
 int launch_mfma_ct(tfhe_ctx* c, const uint32_t* big, D* dig, uint32_t* out, const uint64_t* out_ptrs,
                    uint32_t B, hipStream_t s) {
@@ -486,6 +653,7 @@ int launch_w(tfhe_ctx* c, const void* big, void* dig, void* out, const uint64_t*
         if (c->d_ksk8 && 16 / V <= (int)c->p.ks_t) {
             const uint32_t* b32 = (const uint32_t*)big;
             uint32_t* o32 = (uint32_t*)out;
+            if (V == 4 && c->p.ks_t == 8) return launch_mfma8(c, b32, dig, o32, out_ptrs, B, s);
             if (c->p.ks_t * c->p.ks_base_bits <= 16) return launch_mfma_ks<V, uint16_t, 1>(c, b32, dig, o32, out_ptrs, B, s);
             return launch_mfma_ks<V, uint32_t, 1>(c, b32, dig, o32, out_ptrs, B, s);
         }
