@@ -43,13 +43,16 @@
 // 72% of their peak but needs 2N (k+1)l N limbs operations where the
 // transforms need about 1/100 of them.  Measured on one box, int8 path ->
 // this one, identical bits: n = 630, N = 1024, l = 3, q = 32: 1 ciphertext
-// 8.4 -> 3.5 ms, 256 30.8 -> 3.4 ms, 1024 50 -> 9.8 ms, 4096 77 -> 32 ms;
-// n = 750, N = 2048, l = 4, q = 64: 1 ciphertext 34 -> 18 ms, 256 158 -> 15 ms,
-// 1000 355 -> 61 ms.
+// 8.4 -> 2.9 ms, 256 30.8 -> 3.0 ms, 1024 50 -> 9.1 ms, 4096 77 -> 29.7 ms;
+// n = 750, N = 2048, l = 4, q = 64: 1 ciphertext 34 -> 15.5 ms, 256 158 -> 13.4 ms,
+// 1000 355 -> 53 ms.
 //
-// What bounds it: double-precision vector issue (a wave instruction takes
-// 4 cycles of its SIMD; about 4300 of them per ciphertext and step at
-// N = 1024, l = 3, q = 32) with two waves per SIMD to hide LDS and key latency.
+// What bounds it: double-precision vector issue (about 4200 vector
+// instructions per ciphertext and step at N = 1024, l = 3, q = 32, 3000 of them
+// double precision at 4.3-4.7 cycles of their SIMD; the vector units are 61%
+// busy in a launch of 2048) and the LDS exchanges beside it; for one ciphertext
+// per workgroup the key reads (64 bytes per cycle and CU: 3100 of the 11,000
+// cycles of a step at N = 1024, 12,300 of 42,000 at N = 2048, q = 64, l = 4).
 #include <algorithm>
 #include <cmath>
 
@@ -465,10 +468,11 @@ struct FftArgs {
 // ring of key values, in polynomials; KX of them are requested a transform
 // ahead (AFTER: the next step's once the inverse's twiddles are, else as soon
 // as the ring is free), the others when the transform's registers are free.
-template <typename T_, int R_, int W_, int G_, int L_, int KD_, int KX_, TwiddleSource TWS_, bool AFTER_>
+template <typename T_, int R_, int W_, int G_, int L_, int KD_, int KX_, TwiddleSource TWS_, bool AFTER_,
+          int WPE_ = 2>
 struct Cfg {
     using T = T_;
-    static constexpr int R = R_, W = W_, G = G_, L = L_, KD = KD_, KX = KX_;
+    static constexpr int R = R_, W = W_, G = G_, L = L_, KD = KD_, KX = KX_, WPE = WPE_;
     static constexpr TwiddleSource TWS = TWS_;
     static constexpr bool AFTER = AFTER_;
     using P = Plan<R>;
@@ -480,7 +484,7 @@ struct Cfg {
 };
 
 template <typename CF>
-__global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(2, 2))) void br_fft_kernel(FftArgs a) {
+__global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::WPE, CF::WPE))) void br_fft_kernel(FftArgs a) {
     using T = typename CF::T;
     using P = typename CF::P;
     using WF = typename CF::F;
@@ -858,23 +862,28 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     a.n = (int)c->p.n;
     a.l = (int)c->p.l;
     a.bg_bits = (int)c->p.bg_bits;
-    // Up to 256 ciphertexts (a CU each) one per workgroup, then two, while
-    // that keeps every one resident; four above, two workgroups per CU, which
-    // quarters the key reads (N = 1024: 512 ciphertexts 4.7 ms at two per
-    // workgroup, 1024 9.7 ms at four).  The gadget levels of the named
-    // parameter sets (l = 3 at 32-bit words, 4 at 64-bit) are compile-time, so
-    // that the ring of key values has no conditional loads: with them the
-    // compiler spilled the ring to scratch (N = 1024, 64 ciphertexts
-    // 3.4 -> 2.9 ms; N = 2048, q = 64, 256 ciphertexts 15.4 -> 13.4 ms).  Any
-    // other l loads each polynomial's values when they are needed.
+    // The ciphertexts per workgroup follow the batch, so that every one is
+    // resident if it can be.  At N = 1024, q = 32, on 256 CUs: one (8 waves) up
+    // to a ciphertext per CU (2.9 ms at l = 3), two of the same up to two per CU
+    // (512: 4.7 ms), two in 4 waves, three workgroups per CU, up to six per CU
+    // (1024: 9.1 ms, 1500: 13.1 ms; four per workgroup 9.7 and 15.5 ms), above
+    // that four in 4 waves, two workgroups per CU, whose key reads serve four
+    // (4096: 29.7 ms; 31.4 ms at two).  The gadget levels of the named parameter
+    // sets (l = 3 at 32-bit words, 4 at 64-bit) are compile-time where a ring of
+    // key values is held across a transform: loaded under conditions, the
+    // compiler spilled it to scratch (64 ciphertexts 3.4 -> 2.9 ms; N = 2048,
+    // q = 64, 256 ciphertexts 15.4 -> 13.4 ms).  Any other l loads each
+    // polynomial's values when they are needed.
     const int l = (int)c->p.l;
-    //                                                       T         R   W  G  L  KD KX twiddles AFTER
+    const uint32_t cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
+    //                                                       T         R   W  G  L  KD KX twiddles AFTER WPE
     if (c->q == 32) {
         if (c->p.N == 2048) return l == 3 ? launch_fft_t<Cfg<uint32_t, 16, 8, 1, 3, 2, 1, TW_LDS, true>>(c, a, s)
                                           : launch_fft_t<Cfg<uint32_t, 16, 8, 1, 0, 1, 0, TW_LDS, true>>(c, a, s);
-        if (B > 512) return launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, 0, TW_LDS, false>>(c, a, s);
+        if (B > 6 * cus) return launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, 0, TW_LDS, false>>(c, a, s);
+        if (B > 2 * cus) return launch_fft_t<Cfg<uint32_t, 8, 4, 2, 0, 1, 0, TW_LDS, false, 3>>(c, a, s);
         if (l != 3) return launch_fft_t<Cfg<uint32_t, 8, 8, 1, 0, 2, 0, TW_REG, false>>(c, a, s);
-        return B > 256 ? launch_fft_t<Cfg<uint32_t, 8, 8, 2, 3, 4, 4, TW_REG, false>>(c, a, s)
+        return B > cus ? launch_fft_t<Cfg<uint32_t, 8, 8, 2, 3, 4, 4, TW_REG, false>>(c, a, s)
                        : launch_fft_t<Cfg<uint32_t, 8, 8, 1, 3, 8, 8, TW_REG, true>>(c, a, s);
     }
     if (c->p.N == 2048) return l == 4 ? launch_fft_t<Cfg<uint64_t, 16, 8, 1, 4, 2, 1, TW_GLOBAL, true>>(c, a, s)

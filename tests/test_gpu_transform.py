@@ -50,7 +50,7 @@ def test_transform_path_parity(q, N, l, bg):
     ctx = fs.Context(p, bsk, ksk)
     tv = oracle.gate_testv(p)
     edge = edge_lwe(p, 72)
-    for B in (1, 2, 3, 257, 515):
+    for B in (1, 2, 3, 257, 515, 1539):
         lwe = si.torus(B, 73, B * (p.n + 1), q).reshape(B, p.n + 1)
         if B > len(edge):
             lwe[1:1 + len(edge)] = edge
