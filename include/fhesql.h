@@ -101,11 +101,7 @@ size_t tfhe_ksk_words(const tfhe_params* p);
  * pointers otherwise -- keys generated on the device need no host round trip;
  * sizes in bytes must match tfhe_bsk_words/tfhe_ksk_words), builds the
  * device-only limb-planar Toeplitz form of the BSK and allocates workspace
- * lazily.  With torus_bits = 32 and N = 1024 it also builds, when the device
- * has room, the BSK's 16-byte key windows (16 bytes per byte of the limb
- * form: 968 MB at n = 630, l = 3), from which the blind rotation reads its
- * A fragments directly; without room it stages the key in LDS instead (same
- * output bits).  With N = 1024 or 2048 it also holds the transforms of the
+ * lazily.  With N = 1024 or 2048 it also holds the transforms of the
  * BSK's limbs (16 bytes per coefficient pair and limb: 124 MB at n = 630,
  * N = 1024, l = 3; 590 MB at n = 750, N = 2048, l = 4, torus_bits = 64), from
  * which the transform blind rotation runs; without room the int8 kernels are
@@ -151,12 +147,7 @@ int tfhe_set_kernel(tfhe_ctx* ctx, int kind);
  *                        3 = all blocks of a step, accumulator in global
  *                        memory, when they fit; 4 = one component's blocks
  *                        at a time with component 0 in LDS and the key
- *                        staged in LDS, when it fits.  With the key windows
- *                        of a 1024-coefficient 32-bit context (see
- *                        tfhe_ctx_create) and one row pass, 0 reads the key
- *                        from them instead (no key staging, the second
- *                        component's digits formed while the first
- *                        component's blocks run).
+ *                        staged in LDS, when it fits.
  *                        Every grouping gives the same output bits.
  * The blind-rotation workspace depends on the row pass and digit grouping
  * (several passes with per-group digits add a digit cache).  Direct calls and
@@ -377,7 +368,8 @@ typedef struct sql_sum_query {
     void* d_sum;            /* [w + ceil(log2 rows)][n+1] result */
 } sql_sum_query;
 
-/* hbm_budget_bytes: total device memory the server may account for (keys,
+/* hbm_budget_bytes: total device memory the server may account for (keys --
+ * the transforms of the BSK only with torus_bits = 32 and N = 1024 --,
  * two staging sets, temporaries); max_batch: gates per tick. */
 int sql_server_create(tfhe_ctx* ctx, size_t hbm_budget_bytes, uint32_t max_batch,
                       sql_server** out);

@@ -824,6 +824,7 @@ int setup_t(tfhe_ctx* c, hipStream_t s) {
         c->d_fkey = nullptr;
         return TFHE_OK;
     }
+    c->fkey_bytes = key_bytes;
     int rc;
     if ((rc = hip_check(c, hipMalloc(&c->d_ftw, tw.size() * sizeof(d2)), "hipMalloc twiddles")) ||
         (rc = hip_check(c, hipMemcpy(c->d_ftw, tw.data(), tw.size() * sizeof(d2), hipMemcpyHostToDevice),
