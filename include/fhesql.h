@@ -118,8 +118,9 @@ const char* tfhe_last_error(const tfhe_ctx* ctx);
 /* Select TFHE_KERNEL_MFMA or TFHE_KERNEL_PLAIN for later blind rotations. */
 int tfhe_set_kernel(tfhe_ctx* ctx, int kind);
 /* Tuning knobs (none changes an output bit).  The row pass, the digit
- * grouping and the split groups shape the int8 kernels: setting one of them
- * away from its default runs the blind rotation on those, at any N:
+ * grouping and the split groups shape the int8 kernels: a row pass other than
+ * the ring's default, a digit grouping other than 0, or a positive split
+ * threshold that covers the batch runs the blind rotation on those, at any N:
  *   TFHE_TUNE_MAX_BATCH  maximum ciphertexts per blind-rotation launch when a
  *                        circuit level is split into launches (default 65536);
  *   TFHE_TUNE_ROW_PASS   MFMA kernel row tiles per pass (0 = default for N,

@@ -3,9 +3,10 @@
 It times candidate settings of the library's tuning knobs on the caller's
 own workload and keeps the fastest: ciphertexts per blind-rotation launch
 (how a level's gates are cut into launches), MFMA row tiles per pass (the
-Toeplitz tile height a workgroup covers per pass) and, for rings of 512
-coefficients or more, the batch size below which a blind rotation spreads
-each 16-ciphertext group over many workgroups.  No knob changes an output
+Toeplitz tile height a workgroup covers per pass; at 1024 and 2048
+coefficients the default one stands for the transform kernels) and, for rings
+of 512 coefficients or more, the batch size below which a blind rotation
+spreads each 16-ciphertext group over many workgroups.  No knob changes an output
 bit, so the choice only affects time.  The tile width -- ciphertexts per
 tile -- is the MFMA operand's 16 columns and is not a knob (32 ciphertexts
 per workgroup, two tiles sharing each key fragment, measured no faster at

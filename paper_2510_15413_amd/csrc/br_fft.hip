@@ -846,8 +846,15 @@ int fft_setup(tfhe_ctx* c, hipStream_t s) {
     return TFHE_OK;
 }
 
-bool fft_usable(const tfhe_ctx* c) {
-    return c->d_fkey && c->row_pass == 0 && c->digit_blocks == 0 && c->split_groups < 0;
+// Whether a batch of B takes the transform path: unless a tuning knob asks for
+// a shape of the int8 kernels -- a row pass that is not the ring's default, a
+// digit grouping, or a positive split threshold that covers the batch.  (The
+// default row pass and "never split", which earlier tunings saved, do not.)
+bool fft_usable(const tfhe_ctx* c, uint32_t B) {
+    if (!c->d_fkey || c->digit_blocks != 0) return false;
+    const int default_rp = c->p.N == 2048 ? 8 : c->q == 32 ? 16 : 4;
+    if (c->row_pass != 0 && c->row_pass != default_rp) return false;
+    return !(c->split_groups > 0 && ((uint64_t)B + 15) / 16 <= (uint64_t)c->split_groups);
 }
 
 int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index, void* big_out, uint32_t B,

@@ -11,7 +11,7 @@ int launch_br_mfma(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_
                    void* big_out, uint32_t B, void* ws, size_t ws_cap, hipStream_t s);
 int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index, void* big_out, uint32_t B,
                   hipStream_t s);
-bool fft_usable(const tfhe_ctx* c);
+bool fft_usable(const tfhe_ctx* c, uint32_t B);
 int fft_setup(tfhe_ctx* c, hipStream_t s);
 int launch_br_plain(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index,
                     void* big_out, uint32_t B, hipStream_t s);
@@ -455,7 +455,7 @@ int launch_blind_rotate(tfhe_ctx* c, const void* lwe_in, const void* testv_table
     const void* tv = testv_table ? testv_table : c->d_gate_tv;
     TimedLaunch tl(c, s, 0, B);
     if (c->kernel == TFHE_KERNEL_PLAIN) return launch_br_plain(c, lwe_in, tv, tv_index, big_out, B, s);
-    if (fft_usable(c)) return launch_br_fft(c, lwe_in, tv, tv_index, big_out, B, s);
+    if (fft_usable(c, B)) return launch_br_fft(c, lwe_in, tv, tv_index, big_out, B, s);
     return launch_br_mfma(c, lwe_in, tv, tv_index, big_out, B, ws, ws_cap, s);
 }
 

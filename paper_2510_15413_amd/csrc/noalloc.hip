@@ -11,7 +11,7 @@ int launch_br_mfma(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_
                    void* big_out, uint32_t B, void* ws, size_t ws_cap, hipStream_t s);
 int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index, void* big_out, uint32_t B,
                   hipStream_t s);
-bool fft_usable(const tfhe_ctx* c);
+bool fft_usable(const tfhe_ctx* c, uint32_t B);
 int launch_br_plain(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index,
                     void* big_out, uint32_t B, hipStream_t s);
 
@@ -72,6 +72,6 @@ extern "C" int tfhe_bootstrap_batch_noalloc(tfhe_ctx* c, const void* d_lwe_in, c
     const void* tv = d_testv ? d_testv : c->d_gate_tv;
     hipStream_t s = (hipStream_t)stream;
     if (c->kernel == TFHE_KERNEL_PLAIN) return launch_br_plain(c, d_lwe_in, tv, nullptr, d_out, B, s);
-    if (fft_usable(c)) return launch_br_fft(c, d_lwe_in, tv, nullptr, d_out, B, s);
+    if (fft_usable(c, B)) return launch_br_fft(c, d_lwe_in, tv, nullptr, d_out, B, s);
     return launch_br_mfma(c, d_lwe_in, tv, nullptr, d_out, B, ptr, kScratchBytes, s);
 }

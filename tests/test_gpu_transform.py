@@ -112,3 +112,26 @@ def test_transform_path_look_ups_per_ciphertext():
     ctx.set_tuning(split_groups=-1)
     assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
     ctx.close()
+
+
+@pytest.mark.parametrize("knobs,path", [({}, "transform"), ({"row_pass": 16}, "transform"),
+                                        ({"split_groups": 0}, "transform"),
+                                        ({"row_pass": 16, "split_groups": 0}, "transform"),
+                                        ({"row_pass": 8}, "int8"), ({"digit_blocks": 4}, "int8"),
+                                        ({"split_groups": 1}, "mixed")])
+def test_knobs_and_batch_sizes_keep_the_bits(knobs, path):
+    """Every route a knob selects at the 1024-coefficient ring (the transform
+    path also for the settings that stood for the old default) gives the same
+    bits at batches on both sides of the split threshold."""
+    p = si.Params("knobs", 32, 6, 1, 1024, 7, 3, 2, 8, 20, 25)
+    ctx = fs.Context(p, si.torus(5, 77, p.bsk_words(), 32), np.zeros(p.ksk_words(), dtype=np.uint64))
+    for B in (16, 17, 40):
+        d = to_dev(p, si.torus(B, 78, B * (p.n + 1), 32).reshape(B, p.n + 1))
+        ref, got = empty(p, B, p.N + 1), empty(p, B, p.N + 1)
+        ctx.tfhe_bootstrap_batch(d, ref)
+        ctx.set_tuning(**knobs)
+        ctx.tfhe_bootstrap_batch(d, got)
+        ctx.set_tuning(row_pass=0, digit_blocks=0, split_groups=-1)
+        torch.cuda.synchronize()
+        assert torch.equal(got, ref), (knobs, path, B)
+    ctx.close()
