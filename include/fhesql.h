@@ -77,8 +77,9 @@ typedef struct tfhe_params {
 typedef struct tfhe_ctx tfhe_ctx;
 
 /* Blind-rotation kernel selection: the fast kernels (default) -- exact
- * products by double-precision transforms of key limbs for N = 1024 and 2048,
- * by limb-split int8 MFMA otherwise -- or the plain scalar-integer one.  All
+ * products by double-precision transforms of key limbs for N = 1024 and 2048
+ * (and for batches where it is faster at N = 256 with torus_bits = 32), by
+ * limb-split int8 MFMA otherwise -- or the plain scalar-integer one.  All
  * give identical bits. */
 #define TFHE_KERNEL_MFMA 0
 #define TFHE_KERNEL_PLAIN 1
@@ -101,7 +102,8 @@ size_t tfhe_ksk_words(const tfhe_params* p);
  * pointers otherwise -- keys generated on the device need no host round trip;
  * sizes in bytes must match tfhe_bsk_words/tfhe_ksk_words), builds the
  * device-only limb-planar Toeplitz form of the BSK and allocates workspace
- * lazily.  With N = 1024 or 2048 it also holds the transforms of the
+ * lazily.  With N = 1024 or 2048, or N = 256 and torus_bits = 32, it also
+ * holds the transforms of the
  * BSK's limbs (16 bytes per coefficient pair and limb: 124 MB at n = 630,
  * N = 1024, l = 3; 590 MB at n = 750, N = 2048, l = 4, torus_bits = 64), from
  * which the transform blind rotation runs; without room the int8 kernels are

@@ -1,6 +1,6 @@
 // Blind rotation + sample extraction with exact negacyclic products by
 // double-precision transforms (gfx950), for rings of 1024 and 2048
-// coefficients.
+// coefficients and, at 32-bit words, of 256.
 //
 // TFHE bootstrapping (ePrint 2018/421, Alg. 3 / Sec. 4): for i = 0..n-1,
 //   ACC <- ACC + ExtProd(BSK_i, X^{abar_i} ACC - ACC),
@@ -153,6 +153,43 @@ FHE_DEV void lane_inv(double (&re)[R], double (&im)[R], const double* c, const d
             }
         }
     }
+}
+
+// The first pass (uniform twiddles) backwards, its factors c left to the end:
+// a butterfly keeps y / c, two elements of different factors are combined with
+// their ratio, and element r has to be multiplied by sc[r] (all constants),
+// which the rounding does for nothing.
+template <int R>
+FHE_DEV void lane_inv_first(double (&re)[R], double (&im)[R], double (&sc)[R]) {
+#pragma unroll
+    for (int r = 0; r < R; r++) sc[r] = 1.0;
+#pragma unroll
+    for (int m = Plan<R>::L; m >= 1; m--) {
+        const int half = R >> m;
+#pragma unroll
+        for (int b = 0; b < (1 << (m - 1)); b++) {
+            const int k = m == 1 ? 0 : (1 << (m - 2)) + (b >> 1);
+#pragma unroll
+            for (int x = 0; x < half; x++) {
+                const int i = 2 * b * half + x, j = i + half;
+                const double q = sc[j] / sc[i], t = kT1[k];
+                const double dr = __builtin_fma(-q, re[j], re[i]), di = __builtin_fma(-q, im[j], im[i]);
+                re[i] = __builtin_fma(q, re[j], re[i]);
+                im[i] = __builtin_fma(q, im[j], im[i]);
+                const double pr = __builtin_fma(t, di, dr), pi = __builtin_fma(-t, dr, di);
+                re[j] = b & 1 ? pi : pr;
+                im[j] = b & 1 ? -pr : pi;
+                sc[j] = sc[i] * kC1[k];
+            }
+        }
+    }
+}
+
+// x sc to the nearest integer, as the 64-bit difference from kMagic's bits:
+// integers below 2^51 end up in the low bits of the sum with 1.5 * 2^52
+constexpr double kMagic = 6755399441055744.0;
+FHE_DEV uint64_t nearest(double x, double sc) {
+    return __builtin_bit_cast(uint64_t, __builtin_fma(x, sc, kMagic)) - __builtin_bit_cast(uint64_t, kMagic);
 }
 
 // Exchange lane bit 5 (4) with the register bit that tells a from b.
@@ -399,7 +436,6 @@ struct WaveFft {
         wave_order();
         get_blocks(re, im);
     }
-    FHE_DEV void inverse_first(double (&re)[R], double (&im)[R]) const { lane_inv<R>(re, im, kC1, kT1); }
     // offset of member e of pair g in a buffer
     FHE_DEV static uint32_t pair_off(int e, int g) { return (e * (P::M / 2) + (g ^ (e * 4))) * 16; }
 };
@@ -591,7 +627,6 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
             if (q0 + pp < NB) key_load(kv[pp], i, q0 + pp);
     };
 
-    constexpr double kMagic = 6755399441055744.0;  // 1.5 * 2^52: integers below 2^51 end up in the low bits
     int abv = 0;  // abar of steps 64 (i/64) + lane
     key_ahead(0, 0);
     lds_barrier();
@@ -708,16 +743,15 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
             if (mine) f.inverse_to_first(re, im, tw);
             if (rd + 1 < IR) lds_barrier();
             if (mine) {
-                f.inverse_first(re, im);
+                double sc[R];
+                lane_inv_first<R>(re, im, sc);
                 constexpr int LC = Limb<T>::COUNT;
                 T* acc = acc_ct + (size_t)(o / LC) * N + lane;
                 const int sh = (o % LC) * Limb<T>::BITS;
 #pragma unroll
                 for (int r = 0; r < R; r++) {
-                    const uint64_t vr = __builtin_bit_cast(uint64_t, re[r] + kMagic) - __builtin_bit_cast(uint64_t, kMagic);
-                    const uint64_t vi = __builtin_bit_cast(uint64_t, im[r] + kMagic) - __builtin_bit_cast(uint64_t, kMagic);
-                    atomicAdd(acc + 64 * r, (T)vr << sh);
-                    atomicAdd(acc + 64 * r + M, (T)vi << sh);
+                    atomicAdd(acc + 64 * r, (T)nearest(re[r], sc[r]) << sh);
+                    atomicAdd(acc + 64 * r + M, (T)nearest(im[r], sc[r]) << sh);
                 }
             }
         }
@@ -734,6 +768,296 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
         for (int j = tid; j <= N; j += 64 * W)
             out[(size_t)(ct0 + c) * (N + 1) + j] = j == 0 ? A[0] : j < N ? (T)(0 - A[N - j]) : A[N];
     }
+}
+
+// ---------------------------------------------- small ring (N = 256, q = 32)
+//
+// A transform of M = 128 points takes 16 lanes with 8 points each, so one wave
+// transforms 4 polynomials at a time: the digits of a ciphertext (l = 2: all of
+// them), or its 4 outputs on the way back.  Radix 8, an exchange, radix 8, and
+// the last level in the lane that multiplies (64 pairs, a lane each).  A wave
+// needs no other: no barrier, one wave per workgroup, G ciphertexts per wave
+// that share the key values it reads.
+//
+// Bounded by double-precision issue (530 of about 780 vector instructions per
+// ciphertext and step).  Measured at n = 64, l = 2 against the int8 kernel
+// (whose workgroup runs 16 ciphertexts, so that its time goes in steps of 16
+// per CU): 1 ciphertext 0.447 -> 0.144 ms, 1024 0.467 -> 0.200 ms, 2597
+// 0.489 -> 0.398 ms, 5903 0.844 -> 0.726 ms; 8192 0.896 against 0.934 ms and
+// 65,536 6.74 against 6.96 ms, where the int8 kernel stays (small_pays).
+struct Small {
+    static constexpr int N = 256, M = 128;
+    static constexpr int T4 = 32, TN = 32 + 64;  // twiddle table: [8 blocks][4], [64 pairs]
+};
+
+template <int G>
+constexpr uint32_t small_lds() { return G * (4 * Small::M * 16 + 2 * Small::N * 4); }
+
+// L: gadget levels when compile-time (then all of a step's key values are
+// requested a step ahead when AHEAD), else 0.
+template <int G, int L, bool AHEAD, int WPE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void br_fft256_kernel(FftArgs a) {
+    using T = uint32_t;
+    constexpr int N = Small::N, M = Small::M, LN = 8, OUT = 4;
+    constexpr int KD = AHEAD ? 4 : 1;
+    static_assert(!AHEAD || (L > 0 && 2 * L <= 4), "key values of one pass");
+    const int lane = threadIdx.x;
+    const int n = a.n, l = L ? L : a.l, NB = 2 * l;
+    const int ct0 = blockIdx.x * G;
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    d2* const bufs = (d2*)smem;                       // [G][4 polynomials][M]
+    T* const accs = (T*)(smem + G * 4 * M * 16);      // [G][2][N]
+
+    for (int idx = lane; idx < G * N; idx += 64) {
+        const int c = idx / N, j = idx & (N - 1);
+        const int gi = min(ct0 + c, a.B - 1);
+        const T* lwe = (const T*)a.lwe + (size_t)gi * (n + 1);
+        const int bb = (int)mod_switch<T>(lwe[n], LN + 1);
+        const T* tv = (const T*)a.tv + (size_t)(a.tv_index ? a.tv_index[gi] : 0) * N;
+        accs[c * 2 * N + j] = 0;
+        accs[c * 2 * N + N + j] =
+            monomial_coef<T>([&](int s) -> T { return tv[s]; }, N, (2 * N - bb) & (2 * N - 1), j);
+    }
+
+    // lane: polynomial pl of the pass; point j4 (of 16) or block k, member b0
+    const int pl = lane >> 4, j4 = lane & 15, k = j4 >> 1, b0 = j4 & 1;
+    double c2[4], t2[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const d2 w = a.tw[k * 4 + i];
+        c2[i] = w.x;
+        t2[i] = w.y;
+    }
+    const d2 w4 = a.tw[Small::T4 + lane];
+    // exchange: point j of block k at 16 k + (j ^ 2 k); pairs: member planes of
+    // 64, the second one's index ^ 4
+    const int wr = pl * M + j4, rd = pl * M + k * 16 + (b0 ^ (2 * k)), pr = pl * M + b0 * 64 + (k ^ (b0 * 4));
+
+    const int bgb = a.bg_bits;
+    const int shr = 32 - l * bgb;
+    uint32_t off = 0;
+    for (int p = 0; p < l; p++) off += (uint32_t)(1 << (bgb - 1)) << (p * bgb);
+    const T F = off << shr;
+    const T C = (1u << (shr - 1)) + F;
+
+    const d2* const key0 = a.fkey + lane;  // [n][2l][OUT][2 members][64 pairs]
+    d2 kv[KD][OUT][2];
+    auto key_load = [&](d2 (&v)[OUT][2], int i, int pq) {
+        const d2* kp = key0 + ((size_t)i * NB + pq) * (OUT * M);
+#pragma unroll
+        for (int o = 0; o < OUT; o++)
+#pragma unroll
+            for (int e = 0; e < 2; e++) v[o][e] = kp[o * M + e * 64];
+    };
+    if constexpr (AHEAD) {
+#pragma unroll
+        for (int pp = 0; pp < 2 * L; pp++) key_load(kv[pp], 0, pp);
+    }
+
+    int abv[G];
+    wave_order();
+    for (int i = 0; i < n; i++) {
+        if ((i & 63) == 0) {
+#pragma unroll
+            for (int c = 0; c < G; c++)
+                abv[c] = i + lane < n ? (int)mod_switch<T>(
+                                            ((const T*)a.lwe)[(size_t)min(ct0 + c, a.B - 1) * (n + 1) + i + lane], LN + 1)
+                                      : 0;
+        }
+        double ar[G][OUT][2], ai[G][OUT][2];
+#pragma unroll
+        for (int c = 0; c < G; c++)
+#pragma unroll
+            for (int o = 0; o < OUT; o++)
+#pragma unroll
+                for (int e = 0; e < 2; e++) ar[c][o][e] = ai[c][o][e] = 0;
+        for (int q0 = 0; q0 < NB; q0 += 4) {
+            // digits and transforms of polynomials q0 .. q0 + 3 (a lane's past
+            // the last one repeats it; it is not read)
+            const int pq = min(q0 + pl, NB - 1), u = pq >= l ? 1 : 0;
+            const int pos = shr + (l - 1 - (pq - u * l)) * bgb;
+#pragma unroll
+            for (int c = 0; c < G; c++) {
+                const int ab = __builtin_amdgcn_readlane(abv[c], i & 63);
+                const T* acc = accs + (c * 2 + u) * N;
+                // digit word of coefficient 16 r + x0
+                int x0 = L == 2 ? j4 + (pl & 1) * M : j4;
+                __asm__ volatile("" : "+v"(x0));
+                const T* own = acc + x0;
+                x0 -= ab;
+                auto word = [&](int r) -> int {
+                    const int x = x0 + 16 * r;
+                    const T v = acc[x & (N - 1)];
+                    const T m = (T)(int32_t)__builtin_amdgcn_sbfe(x, LN, 1);
+                    return (int)(((C - own[16 * r]) + ((v ^ m) - m)) ^ F);
+                };
+                double re[8], im[8];
+#pragma unroll
+                for (int r = 0; r < 8; r++) {
+                    int zr, zi;
+                    if constexpr (L == 2) {
+                        // the two levels of a component (lane rows 2u, 2u + 1)
+                        // form a half of its words each and swap copies
+                        const int z = word(r);
+                        const auto zz = __builtin_amdgcn_permlane16_swap(z, z, false, false);
+                        zr = (int)zz[0];
+                        zi = (int)zz[1];
+                    } else {
+                        zr = word(r);
+                        zi = word(r + 8);
+                    }
+                    re[r] = (double)(int)__builtin_amdgcn_sbfe(zr, pos, bgb);
+                    im[r] = (double)(int)__builtin_amdgcn_sbfe(zi, pos, bgb);
+                }
+                d2* buf = bufs + c * 4 * M;
+                lane_fwd<8>(re, im, kC1, kT1);
+#pragma unroll
+                for (int r = 0; r < 8; r++) buf[(wr ^ (2 * r)) + r * 16] = d2{re[r], im[r]};
+                wave_order();
+#pragma unroll
+                for (int r = 0; r < 8; r++) {
+                    const d2 v = buf[rd ^ (2 * r)];
+                    re[r] = v.x;
+                    im[r] = v.y;
+                }
+                lane_fwd<8>(re, im, c2, t2);
+                wave_order();
+#pragma unroll
+                for (int r = 0; r < 8; r++) buf[pr + r * 8] = d2{re[r], im[r]};
+            }
+            wave_order();
+#pragma unroll
+            for (int pp = 0; pp < 4; pp++) {
+                if (L ? pp >= 2 * L : q0 + pp >= NB) break;
+                if (!AHEAD) key_load(kv[0], i, q0 + pp);
+#pragma unroll
+                for (int c = 0; c < G; c++) {
+                    const d2 x = bufs[(c * 4 + pp) * M + lane], y = bufs[(c * 4 + pp) * M + 64 + (lane ^ 4)];
+                    double dr[2] = {x.x, y.x}, di[2] = {x.y, y.y};
+                    bf_fwd<false>(dr[0], di[0], dr[1], di[1], w4.x, w4.y);
+#pragma unroll
+                    for (int o = 0; o < OUT; o++)
+#pragma unroll
+                        for (int e = 0; e < 2; e++) {
+                            const d2 w = kv[pp % KD][o][e];
+                            ar[c][o][e] = __builtin_fma(dr[e], w.x, ar[c][o][e]);
+                            ai[c][o][e] = __builtin_fma(dr[e], w.y, ai[c][o][e]);
+                            ar[c][o][e] = __builtin_fma(-di[e], w.y, ar[c][o][e]);
+                            ai[c][o][e] = __builtin_fma(di[e], w.x, ai[c][o][e]);
+                        }
+                }
+                if constexpr (AHEAD) key_load(kv[pp], i + 1 < n ? i + 1 : i, pp);
+            }
+            wave_order();
+        }
+        // back: the lanes of group pl transform output pl (component pl / 2, limb pl % 2)
+#pragma unroll
+        for (int c = 0; c < G; c++) {
+            d2* buf = bufs + c * 4 * M;
+#pragma unroll
+            for (int o = 0; o < OUT; o++) {
+                bf_inv<false>(ar[c][o][0], ai[c][o][0], ar[c][o][1], ai[c][o][1], w4.x, w4.y);
+                buf[o * M + lane] = d2{ar[c][o][0], ai[c][o][0]};
+                buf[o * M + 64 + (lane ^ 4)] = d2{ar[c][o][1], ai[c][o][1]};
+            }
+            wave_order();
+            double re[8], im[8];
+#pragma unroll
+            for (int r = 0; r < 8; r++) {
+                const d2 v = buf[pr + r * 8];
+                re[r] = v.x;
+                im[r] = v.y;
+            }
+            lane_inv<8>(re, im, c2, t2);
+            wave_order();
+#pragma unroll
+            for (int r = 0; r < 8; r++) buf[rd ^ (2 * r)] = d2{re[r], im[r]};
+            wave_order();
+#pragma unroll
+            for (int r = 0; r < 8; r++) {
+                const d2 v = buf[(wr ^ (2 * r)) + r * 16];
+                re[r] = v.x;
+                im[r] = v.y;
+            }
+            double sc[8];
+            lane_inv_first<8>(re, im, sc);
+            T* acc = accs + (c * 2 + (pl >> 1)) * N + j4;
+            const int sh = (pl & 1) * 16;
+#pragma unroll
+            for (int r = 0; r < 8; r++) {
+                atomicAdd(acc + 16 * r, (T)nearest(re[r], sc[r]) << sh);
+                atomicAdd(acc + 16 * r + M, (T)nearest(im[r], sc[r]) << sh);
+            }
+        }
+        wave_order();
+    }
+
+    T* out = (T*)a.out;
+    for (int c = 0; c < G && ct0 + c < a.B; c++) {
+        const T* A = accs + c * 2 * N;
+        for (int j = lane; j <= N; j += 64)
+            out[(size_t)(ct0 + c) * (N + 1) + j] = j == 0 ? A[0] : j < N ? 0 - A[N - j] : A[N];
+    }
+}
+
+// Key spectra of the small ring: 16 lanes per (polynomial, limb), 4 per wave.
+__global__ __launch_bounds__(64) void fft256_key_kernel(const uint32_t* bsk, const d2* tw, d2* fkey, int total) {
+    constexpr int N = Small::N, M = Small::M;
+    __shared__ d2 buf[4 * M];
+    const int lane = threadIdx.x, pl = lane >> 4, j4 = lane & 15, k = j4 >> 1, b0 = j4 & 1;
+    const int id = min((int)blockIdx.x * 4 + pl, total - 1);  // polynomial * 2 + limb
+    const uint32_t* K = bsk + (size_t)(id >> 1) * N;
+    const int limb = id & 1;
+    double c2[4], t2[4];
+    for (int i = 0; i < 4; i++) {
+        c2[i] = tw[k * 4 + i].x;
+        t2[i] = tw[k * 4 + i].y;
+    }
+    auto part = [&](int j) -> double {
+        const uint32_t x = K[j];
+        const int lo = (int16_t)x;
+        return limb ? (double)(int16_t)((x - (uint32_t)lo) >> 16) : (double)lo;
+    };
+    double re[8], im[8];
+#pragma unroll
+    for (int r = 0; r < 8; r++) {
+        re[r] = part(16 * r + j4);
+        im[r] = part(16 * r + j4 + M);
+    }
+    const int wr = pl * M + j4, rd = pl * M + k * 16 + (b0 ^ (2 * k)), pr = pl * M + b0 * 64 + (k ^ (b0 * 4));
+    lane_fwd<8>(re, im, kC1, kT1);
+#pragma unroll
+    for (int r = 0; r < 8; r++) buf[(wr ^ (2 * r)) + r * 16] = d2{re[r], im[r]};
+    wave_order();
+#pragma unroll
+    for (int r = 0; r < 8; r++) {
+        const d2 v = buf[rd ^ (2 * r)];
+        re[r] = v.x;
+        im[r] = v.y;
+    }
+    lane_fwd<8>(re, im, c2, t2);
+    wave_order();
+#pragma unroll
+    for (int r = 0; r < 8; r++) buf[pr + r * 8] = d2{re[r], im[r]};
+    wave_order();
+    const d2 w = tw[Small::T4 + lane];
+    constexpr double scale = 1.0 / M;
+    for (int q = 0; q < 4 && (int)blockIdx.x * 4 + q < total; q++) {
+        const d2 x = buf[q * M + lane], y = buf[q * M + 64 + (lane ^ 4)];
+        double xr = x.x, xi = x.y, yr = y.x, yi = y.y;
+        bf_fwd<false>(xr, xi, yr, yi, w.x, w.y);
+        d2* out = fkey + (size_t)(blockIdx.x * 4 + q) * M;
+        out[lane] = d2{xr * scale, xi * scale};
+        out[64 + lane] = d2{yr * scale, yi * scale};
+    }
+}
+
+template <int G, int L, bool AHEAD, int WPE>
+int launch_small(tfhe_ctx* c, const FftArgs& a, hipStream_t s) {
+    auto k = br_fft256_kernel<G, L, AHEAD, WPE>;
+    if (L && L != a.l) return ctx_fail(c, TFHE_EINVAL, "transform kernel of another level count");
+    hipLaunchKernelGGL(k, dim3((a.B + G - 1) / G), dim3(64), small_lds<G>(), s, a);
+    return hip_check(c, hipGetLastError(), "launch br_fft256");
 }
 
 template <typename CF>
@@ -756,19 +1080,20 @@ d2 twiddle(long double turns) {
 // Angles (in turns): after t levels the block with path bits d1..dt is mod
 // X^m - e^{2 pi i theta}, theta = 1/(4 2^t) + sum_i d_i 2^{i-1-t}, and the next
 // level's twiddle has the angle theta/2.
+long double theta(const std::vector<int>& d) {
+    const int t = (int)d.size();
+    long double x = 0.25L;
+    for (int i = 0; i < t; i++) x += d[i] * (long double)(1 << i);
+    return x / (long double)(1 << t);
+}
+void bits(std::vector<int>& d, int v, int count) {  // first path bit = top bit
+    for (int b = count - 1; b >= 0; b--) d.push_back((v >> b) & 1);
+}
+
+// the second pass's twiddles of every block of the first
 template <int R>
-std::vector<d2> twiddle_table() {
+void second_pass(d2* tw) {
     using P = Plan<R>;
-    std::vector<d2> tw(P::TN);
-    auto theta = [](std::vector<int> d) {
-        const int t = (int)d.size();
-        long double x = 0.25L;
-        for (int i = 0; i < t; i++) x += d[i] * (long double)(1 << i);
-        return x / (long double)(1 << t);
-    };
-    auto bits = [](std::vector<int>& d, int v, int count) {  // first path bit = top bit
-        for (int b = count - 1; b >= 0; b--) d.push_back((v >> b) & 1);
-    };
     for (int k = 0; k < R; k++)
         for (int m = 1; m <= P::L; m++)
             for (int q = 0; q < (m == 1 ? 1 : 1 << (m - 2)); q++) {
@@ -780,6 +1105,13 @@ std::vector<d2> twiddle_table() {
                 }
                 tw[(size_t)k * P::NT2 + (m == 1 ? 0 : (1 << (m - 2)) + q)] = twiddle(theta(d) / 2);
             }
+}
+
+template <int R>
+std::vector<d2> twiddle_table() {
+    using P = Plan<R>;
+    std::vector<d2> tw(P::TN);
+    second_pass<R>(tw.data());
     for (int x = 0; x < 32; x++)
         for (int q = 0; q < P::NT3; q++) {
             std::vector<int> d;
@@ -813,37 +1145,79 @@ std::vector<d2> twiddle_table() {
     return tw;
 }
 
-template <typename T, int R>
-int setup_t(tfhe_ctx* c, hipStream_t s) {
-    using P = Plan<R>;
-    const std::vector<d2> tw = twiddle_table<R>();
-    const size_t polys = (size_t)c->p.n * 2 * c->p.l * 2;
-    const size_t key_bytes = polys * Limb<T>::COUNT * P::M * sizeof(d2);
-    if (hipMalloc(&c->d_fkey, key_bytes) != hipSuccess) {
+// The small ring: [8 blocks][4] and the last level's [64 pairs], path bits (k, e).
+std::vector<d2> small_table() {
+    std::vector<d2> tw(Small::TN);
+    second_pass<8>(tw.data());
+    for (int g = 0; g < 64; g++) {
+        std::vector<int> d;
+        bits(d, g & 7, 3);
+        bits(d, g >> 3, 3);
+        tw[Small::T4 + g] = twiddle(theta(d) / 2);
+    }
+    return tw;
+}
+
+// Allocates the key spectra of `per_poly` values per key polynomial with the
+// twiddles behind them, and uploads those; no room leaves d_fkey null.
+int setup_tables(tfhe_ctx* c, size_t per_poly, const std::vector<d2>& tw) {
+    const size_t key_bytes = (size_t)c->p.n * 2 * c->p.l * 2 * per_poly * sizeof(d2);
+    if (hipMalloc(&c->d_fkey, key_bytes + tw.size() * sizeof(d2)) != hipSuccess) {
         (void)hipGetLastError();
         c->d_fkey = nullptr;
         return TFHE_OK;
     }
     c->fkey_bytes = key_bytes;
-    int rc;
-    if ((rc = hip_check(c, hipMalloc(&c->d_ftw, tw.size() * sizeof(d2)), "hipMalloc twiddles")) ||
-        (rc = hip_check(c, hipMemcpy(c->d_ftw, tw.data(), tw.size() * sizeof(d2), hipMemcpyHostToDevice),
-                        "copy twiddles")))
-        return rc;
+    c->d_ftw = (uint8_t*)c->d_fkey + key_bytes;
+    return hip_check(c, hipMemcpy(c->d_ftw, tw.data(), tw.size() * sizeof(d2), hipMemcpyHostToDevice),
+                     "copy twiddles");
+}
+
+template <typename T, int R>
+int setup_t(tfhe_ctx* c, hipStream_t s) {
+    constexpr int LC = Limb<T>::COUNT;
+    const int rc = setup_tables(c, (size_t)LC * Plan<R>::M, twiddle_table<R>());
+    if (rc || !c->d_fkey) return rc;
     auto k = fft_key_kernel<T, R>;
-    hipLaunchKernelGGL(k, dim3((unsigned)(polys * Limb<T>::COUNT)), dim3(64), 0, s, (const T*)c->d_bsk,
-                       (const d2*)c->d_ftw, (d2*)c->d_fkey);
+    hipLaunchKernelGGL(k, dim3(c->p.n * 2 * c->p.l * 2 * LC), dim3(64), 0, s, (const T*)c->d_bsk, (const d2*)c->d_ftw,
+                       (d2*)c->d_fkey);
     return hip_check(c, hipGetLastError(), "launch fft_key");
+}
+
+int setup_small(tfhe_ctx* c, hipStream_t s) {
+    const int rc = setup_tables(c, 2 * Small::M, small_table());
+    if (rc || !c->d_fkey) return rc;
+    const int total = (int)(c->p.n * 2 * c->p.l * 2 * 2);
+    hipLaunchKernelGGL(fft256_key_kernel, dim3((total + 3) / 4), dim3(64), 0, s, (const uint32_t*)c->d_bsk,
+                       (const d2*)c->d_ftw, (d2*)c->d_fkey, total);
+    return hip_check(c, hipGetLastError(), "launch fft256_key");
 }
 
 }  // namespace
 
 // Key spectra and twiddles of a context whose ring has 1024 or 2048
-// coefficients (none without room for them: the int8 path is used then).
+// coefficients, or 256 at 32-bit words (none without room for them: the int8
+// path is used then).
 int fft_setup(tfhe_ctx* c, hipStream_t s) {
+    if (c->p.N == 256 && c->q == 32) return setup_small(c, s);
     if (c->p.N == 1024) return c->q == 32 ? setup_t<uint32_t, 8>(c, s) : setup_t<uint64_t, 8>(c, s);
     if (c->p.N == 2048) return c->q == 32 ? setup_t<uint32_t, 16>(c, s) : setup_t<uint64_t, 16>(c, s);
     return TFHE_OK;
+}
+
+// The small ring's transform kernel against the int8 one: linear in the batch
+// against steps of 16 ciphertexts per CU.  At n = 64, l = 2 on 256 CUs (step
+// 4096), int8 / transform in ms: 2597 0.489 / 0.398, 4096 0.521 / 0.530, 5000
+// 0.787 / 0.735, 6700 0.84 / 0.93, 9209 1.37 / 1.16, 10,400 1.38 / 1.34, 14,100
+// 1.73 / 1.65, 17,800 2.24 / 2.09, 21,500 2.62 / 2.53, 32,768 3.57 / 3.64.  So it
+// is taken in the first three quarters of the first step and the first half
+// of the next five.  At other level counts (l = 3: 2048 0.784 / 0.489, 5: 1.21 /
+// 0.69, 1: 0.321 / 0.293) up to half a step.
+static bool small_pays(const tfhe_ctx* c, uint32_t B) {
+    const uint64_t step = 16ull * (c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256);
+    if (c->p.l != 2) return B <= step / 2;
+    const uint64_t full = B / step, rem = B % step;
+    return full == 0 ? rem <= step * 3 / 4 : full <= 5 && rem <= step / 2 && rem > 0;
 }
 
 // Whether a batch of B takes the transform path: unless a tuning knob asks for
@@ -852,7 +1226,8 @@ int fft_setup(tfhe_ctx* c, hipStream_t s) {
 // default row pass and "never split", which earlier tunings saved, do not.)
 bool fft_usable(const tfhe_ctx* c, uint32_t B) {
     if (!c->d_fkey || c->digit_blocks != 0) return false;
-    const int default_rp = c->p.N == 2048 ? 8 : c->q == 32 ? 16 : 4;
+    if (c->p.N == 256 && !small_pays(c, B)) return false;
+    const int default_rp = c->p.N == 2048 ? 8 : c->q == 64 || c->p.N == 256 ? 4 : 16;
     if (c->row_pass != 0 && c->row_pass != default_rp) return false;
     return !(c->split_groups > 0 && ((uint64_t)B + 15) / 16 <= (uint64_t)c->split_groups);
 }
@@ -884,6 +1259,12 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     // polynomial's values when they are needed.
     const int l = (int)c->p.l;
     const uint32_t cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
+    if (c->p.N == 256) {
+        // one ciphertext per wave with a step's key values requested ahead while
+        // every wave has its SIMD slot (12 per CU), two per wave above
+        if (l != 2) return launch_small<1, 0, false, 3>(c, a, s);
+        return B <= 12 * cus ? launch_small<1, 2, true, 2>(c, a, s) : launch_small<2, 2, false, 2>(c, a, s);
+    }
     //                                                       T         R   W  G  L  KD KX twiddles AFTER WPE
     if (c->q == 32) {
         if (c->p.N == 2048) return l == 3 ? launch_fft_t<Cfg<uint32_t, 16, 8, 1, 3, 2, 1, TW_LDS, true>>(c, a, s)

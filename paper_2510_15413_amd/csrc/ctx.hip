@@ -296,7 +296,6 @@ extern "C" void tfhe_ctx_destroy(tfhe_ctx* c) {
     if (c->d_bsk) hipFree(c->d_bsk);
     if (c->d_bsk8) hipFree(c->d_bsk8);
     if (c->d_fkey) hipFree(c->d_fkey);
-    if (c->d_ftw) hipFree(c->d_ftw);
     if (c->d_ksk) hipFree(c->d_ksk);
     if (c->d_ksk8) hipFree(c->d_ksk8);
     if (c->d_gate_tv) hipFree(c->d_gate_tv);

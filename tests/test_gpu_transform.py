@@ -1,4 +1,5 @@
-"""The transform blind rotation (rings of 1024 and 2048 coefficients): bit for
+"""The transform blind rotation (rings of 1024 and 2048 coefficients, and of 256
+at 32-bit words): bit for
 bit the int8 path on every ciphertext and the oracle on a few, at the edges of
 its launch shapes (one, two or four ciphertexts per workgroup, ragged last
 workgroup) and of the gadget (one level, an odd count, more polynomials than
@@ -42,7 +43,8 @@ def both_paths(p, ctx, d, tv=None):
 
 @pytest.mark.parametrize("q,N,l,bg", [(32, 1024, 3, 7), (32, 1024, 1, 8), (32, 1024, 5, 6), (32, 1024, 31, 1),
                                       (32, 2048, 3, 8), (32, 2048, 5, 6), (64, 1024, 4, 6), (64, 1024, 1, 8),
-                                      (64, 2048, 4, 6), (64, 2048, 3, 8), (64, 2048, 5, 6), (64, 2048, 1, 1)])
+                                      (64, 2048, 4, 6), (64, 2048, 3, 8), (64, 2048, 5, 6), (64, 2048, 1, 1),
+                                      (32, 256, 2, 8), (32, 256, 1, 8), (32, 256, 3, 7), (32, 256, 31, 1)])
 def test_transform_path_parity(q, N, l, bg):
     p = si.Params(f"t{q}_{N}", q, 5, 1, N, bg, l, 2, 8, 20, 25)
     bsk = si.torus(7, 71 + l, p.bsk_words(), q)
@@ -64,7 +66,7 @@ def test_transform_path_parity(q, N, l, bg):
 
 
 @pytest.mark.parametrize("q,N,l,bg", [(32, 1024, 3, 7), (32, 2048, 3, 8), (64, 1024, 3, 8), (64, 2048, 4, 6),
-                                      (64, 2048, 3, 8)])
+                                      (64, 2048, 3, 8), (32, 256, 2, 8), (32, 256, 3, 8)])
 @pytest.mark.parametrize("sign", [1, -1])
 def test_transform_path_largest_sums(q, N, l, bg, sign):
     """Every key limb at the end of its range and, in the first step, every
@@ -134,4 +136,29 @@ def test_knobs_and_batch_sizes_keep_the_bits(knobs, path):
         ctx.set_tuning(row_pass=0, digit_blocks=0, split_groups=-1)
         torch.cuda.synchronize()
         assert torch.equal(got, ref), (knobs, path, B)
+    ctx.close()
+
+
+@pytest.mark.parametrize("l,bg", [(2, 8), (3, 7)])
+def test_small_ring_batches_on_both_sides_of_the_rule(l, bg):
+    """At the 256-coefficient ring the batch decides between the transform and
+    the int8 kernel: around the sizes where it changes (and the step sizes of
+    the int8 kernel) every ciphertext has the bits it has in a small batch."""
+    p = si.Params("small", 32, 9, 1, 256, bg, l, 2, 5, 20, 25)
+    bsk = si.torus(11, 79, p.bsk_words(), 32)
+    ctx = fs.Context(p, bsk, np.zeros(p.ksk_words(), dtype=np.uint64))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    step = 16 * cus
+    top = step + step // 2 + 1
+    lwe = si.torus(12, 80, 777 * (p.n + 1), 32).reshape(777, p.n + 1)
+    d = to_dev(p, np.tile(lwe, (top // 777 + 1, 1))[:top])
+    ref = torch.cat([both_paths(p, ctx, d[:777])[0]] * (top // 777 + 1))[:top]
+    tv = oracle.gate_testv(p)
+    for i in (0, 776):
+        assert np.array_equal(from_dev(p, ref)[i], oracle.bootstrap(p, bsk, lwe[i], tv))
+    for B in (step // 2, step // 2 + 1, 12 * cus, 12 * cus + 1, step, step + 1, top - 1, top):
+        got = empty(p, B, p.N + 1)
+        ctx.tfhe_bootstrap_batch(d[:B].contiguous(), got)
+        torch.cuda.synchronize()
+        assert torch.equal(got, ref[:B]), B
     ctx.close()
