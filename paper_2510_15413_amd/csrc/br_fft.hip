@@ -41,18 +41,22 @@
 //
 // What it is for: the dense Toeplitz product on the int8 matrix cores ran at
 // 72% of their peak but needs 2N (k+1)l N limbs operations where the
-// transforms need about 1/100 of them.  Measured on one box, int8 path ->
-// this one, identical bits: n = 630, N = 1024, l = 3, q = 32: 1 ciphertext
-// 8.4 -> 2.9 ms, 256 30.8 -> 3.0 ms, 1024 50 -> 9.1 ms, 4096 77 -> 29.7 ms;
-// n = 750, N = 2048, l = 4, q = 64: 1 ciphertext 34 -> 15.5 ms, 256 158 -> 13.4 ms,
-// 1000 355 -> 53 ms.
+// transforms need about 1/100 of them.  Measured, int8 path -> this one,
+// identical bits: n = 630, N = 1024, l = 3, q = 32: 1 ciphertext 8.4 -> 2.66 ms,
+// 256 30.8 -> 2.70 ms, 1024 50 -> 9.1 ms, 4096 77 -> 30.5 ms; n = 750, N = 2048,
+// l = 4, q = 64: 1 ciphertext 34 -> 10.7 ms, 256 158 -> 10.6 ms, 1000 355 -> 42.6 ms.
 //
 // What bounds it: double-precision vector issue (about 4200 vector
 // instructions per ciphertext and step at N = 1024, l = 3, q = 32, 3000 of them
 // double precision at 4.3-4.7 cycles of their SIMD; the vector units are 61%
 // busy in a launch of 2048) and the LDS exchanges beside it; for one ciphertext
-// per workgroup the key reads (64 bytes per cycle and CU: 3100 of the 11,000
-// cycles of a step at N = 1024, 12,300 of 42,000 at N = 2048, q = 64, l = 4).
+// per workgroup the chain of a step (digits, transform, products, transform
+// back, three barriers) and the key reads (64 bytes per cycle and CU: 3100 of
+// the 10,000 cycles of a step at N = 1024, 12,300 of 33,000 at N = 2048, q = 64,
+// l = 4), which find their lines in L2: the workgroups of an XCD ask for a
+// step's lines together, each a share, while they transform the step before
+// back.  Values of the next step held in registers across its transforms, as
+// before that, cost more than the L2 hits do now (B = 1 2.87 ms).
 #include <algorithm>
 #include <cmath>
 
@@ -501,18 +505,25 @@ struct FftArgs {
 };
 
 // One configuration: W waves and G ciphertexts per workgroup; KD: a thread's
-// ring of key values, in polynomials; KX of them are requested a transform
-// ahead (AFTER: the next step's once the inverse's twiddles are, else as soon
-// as the ring is free), the others when the transform's registers are free.
-template <typename T_, int R_, int W_, int G_, int L_, int KD_, int KX_, TwiddleSource TWS_, bool AFTER_,
-          int WPE_ = 2>
+// ring of key values, in polynomials, filled when the transform's registers are
+// free.
+template <typename T_, int R_, int W_, int G_, int L_, int KD_, TwiddleSource TWS_, int WPE_ = 2>
 struct Cfg {
     using T = T_;
-    static constexpr int R = R_, W = W_, G = G_, L = L_, KD = KD_, KX = KX_, WPE = WPE_;
+    static constexpr int R = R_, W = W_, G = G_, L = L_, KD = KD_, WPE = WPE_;
     static constexpr TwiddleSource TWS = TWS_;
-    static constexpr bool AFTER = AFTER_;
     using P = Plan<R>;
     using F = WaveFft<R, TWS>;
+    // Key lines into L2 a step ahead (8-wave workgroups; with 4 waves, several
+    // workgroups per CU hide the latency: 1500 ciphertexts 13.6 ms both ways).
+    // Held by lane AHEAD at a time by waves W/2.., a step's lines need HELP
+    // workgroups, 8 XCDs' worth; a smaller batch is topped up with copies.
+    // Without the lines, B = 1 took 3.07 ms (3.62 with the key in HBM), at N =
+    // 2048, q = 64 15.5 ms; without copies 2.98 (3.33) and 13.8; now 2.65 (2.64)
+    // and 10.7 (at 16 copies 13.0, at 32 11.5, at 128 10.6).
+    static constexpr int HELP = W == 8 && G == 1 ? (R == 8 ? 16 : 64) : 0;
+    static constexpr int LINES = 2 * (L ? L : Limb<T>::COUNT + 1) * 2 * Limb<T>::COUNT * P::M / 8;
+    static constexpr int AHEAD = W < 8 ? 0 : HELP ? (LINES + HELP / 8 * 256 - 1) / (HELP / 8 * 256) : 1;
     static constexpr uint32_t BUF = P::M * 16;                            // bytes of a wave's buffer
     static constexpr uint32_t ACC = W * BUF;                              // accumulators [G][2][N]
     static constexpr uint32_t TW = ACC + G * 2 * P::N * (uint32_t)sizeof(T);  // twiddles (TW_LDS)
@@ -524,7 +535,7 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
     using T = typename CF::T;
     using P = typename CF::P;
     using WF = typename CF::F;
-    constexpr int R = CF::R, W = CF::W, G = CF::G, KD = CF::KD, KX = CF::KX;
+    constexpr int R = CF::R, W = CF::W, G = CF::G, KD = CF::KD;
     constexpr int N = P::N, M = P::M, LN = __builtin_ctz(N);
     constexpr int Q = Torus<T>::Q;
     constexpr int OUT = 2 * Limb<T>::COUNT;       // outputs: component, limb
@@ -534,11 +545,12 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
     constexpr int IR = (OUT + PPR - 1) / PPR;     // inverse rounds
     static_assert(W % G == 0 && 64 * W % (M / 2) == 0 && OUT % OS == 0, "work split");
     static_assert(OS == 1 || PPR >= OUT, "one inverse round when the outputs are split over threads");
-    static_assert(PPR % KD == 0 && KX <= KD, "key ring");
+    static_assert(PPR % KD == 0, "key ring");
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = a.n, l = CF::L ? CF::L : a.l, NB = 2 * l;
-    const int ct0 = blockIdx.x * G;
+    // copies (HELP) work on a ciphertext of the batch again and store nothing
+    const int ct0 = CF::HELP ? blockIdx.x % a.B : blockIdx.x * G;
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     T* accs = (T*)(smem + CF::ACC);  // [G][2][N]
@@ -620,15 +632,29 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
 #pragma unroll
             for (int e = 0; e < 2; e++) k[o][e] = kp[o * M + e * (M / 2)];
     };
-    // the first KX polynomials of round (i, q0)
-    auto key_ahead = [&](int i, int q0) {
+    // Key lines of step i, one dword of each, so that they are in this XCD's L2
+    // when the step loads them.  Consecutive workgroups run on different XCDs:
+    // workgroups 8 apart share the lines, and every fourth of a share is a wave's.
+    constexpr int AHEAD = CF::AHEAD;
+    uint32_t line[AHEAD ? AHEAD : 1] = {};
+    const int sharers = min(((int)gridDim.x + 7) / 8, 32);
+    const int lines = NB * OUT * M / 8, share = (lines + sharers - 1) / sharers;
+    const int line0 = (int)(blockIdx.x / 8) % sharers * share, line1 = min(line0 + share, lines);
+    auto request_lines = [&](int i) {
+        if (!AHEAD || wave < W / 2) return;
+        const uint8_t* kb = (const uint8_t*)(a.fkey + (size_t)min(i, n - 1) * NB * OUT * M);
 #pragma unroll
-        for (int pp = 0; pp < KX; pp++)
-            if (q0 + pp < NB) key_load(kv[pp], i, q0 + pp);
+        for (int t = 0; t < AHEAD; t++) {
+            const int x = line0 + (wave - W / 2 + t * (W / 2)) * 64;
+            if (x < line1) line[t] = *(const uint32_t*)(kb + (size_t)min(x + lane, line1 - 1) * 128);
+        }
+    };
+    auto lines_arrived = [&] {
+#pragma unroll
+        for (int t = 0; t < AHEAD; t++) __asm__ volatile("" ::"v"(line[t]));
     };
 
     int abv = 0;  // abar of steps 64 (i/64) + lane
-    key_ahead(0, 0);
     lds_barrier();
     for (int i = 0; i < n; i++) {
         if ((i & 63) == 0) abv = live && i + lane < n ? (int)mod_switch<T>(lwe[i + lane], LN + 1) : 0;
@@ -678,6 +704,7 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
                 form(z, u, ab);
                 for (int p = 0; p < l; p++) {
                     transform(z, p);
+                    if (p + u == 0) lines_arrived();
                     __builtin_amdgcn_sched_barrier(0);  // (not earlier: the transform needs the registers)
                     key_load(kv[0], i, u * l + p);
                     lds_barrier();
@@ -695,13 +722,12 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
                     form(z, u, ab);
                     transform(z, q0 + pq0 - u * l);
                 }
+                if (q0 == 0) lines_arrived();
                 __builtin_amdgcn_sched_barrier(0);  // (not earlier: the transform needs the registers)
 #pragma unroll
-                for (int pp = KX; pp < KD; pp++)
+                for (int pp = 0; pp < KD; pp++)
                     if (q0 + pp < NB) key_load(kv[pp], i, q0 + pp);
                 lds_barrier();
-                const bool last = q0 + PPR >= NB;
-                const int ni = last ? (i + 1 < n ? i + 1 : 0) : i, nq = last ? 0 : q0 + PPR;
 #pragma unroll
                 for (int pp = 0; pp < PPR; pp++) {
                     if (q0 + pp < NB) {
@@ -709,11 +735,7 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
                         pairs(x, y, pp);
                         products(x, y, kv[pp % KD]);
                     }
-                    if (pp + KD < PPR) {
-                        if (q0 + pp + KD < NB) key_load(kv[pp % KD], i, q0 + pp + KD);
-                    } else if (pp + KD - PPR < KX && !(CF::AFTER && last)) {
-                        if (nq + pp + KD - PPR < NB) key_load(kv[pp % KD], ni, nq + pp + KD - PPR);
-                    }
+                    if (pp + KD < PPR && q0 + pp + KD < NB) key_load(kv[pp % KD], i, q0 + pp + KD);
                 }
                 lds_barrier();
             }
@@ -739,7 +761,7 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
             double re[R], im[R];
             typename WF::Twiddles tw;
             f.request(tw);
-            if (CF::AFTER && rd == 0) key_ahead(i + 1 < n ? i + 1 : 0, 0);
+            if (rd == 0) request_lines(i + 1);
             if (mine) f.inverse_to_first(re, im, tw);
             if (rd + 1 < IR) lds_barrier();
             if (mine) {
@@ -762,6 +784,7 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
 
     // ---- sample extraction: a'_0 = A[0], a'_j = -A[N-j], b' = B[0]
     lds_barrier();
+    if (CF::HELP && (int)blockIdx.x >= a.B) return;
     T* out = (T*)a.out;
     for (int c = 0; c < G && ct0 + c < a.B; c++) {
         const T* A = accs + (size_t)c * 2 * N;
@@ -1067,7 +1090,7 @@ int launch_fft_t(tfhe_ctx* c, const FftArgs& a, hipStream_t s) {
     hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)CF::LDS);
     if (e != hipSuccess) return hip_check(c, e, "hipFuncSetAttribute(br_fft)");
     if (CF::L && CF::L != a.l) return ctx_fail(c, TFHE_EINVAL, "transform kernel of another level count");
-    hipLaunchKernelGGL(k, dim3((a.B + CF::G - 1) / CF::G), dim3(64 * CF::W), CF::LDS, s, a);
+    hipLaunchKernelGGL(k, dim3(std::max((a.B + CF::G - 1) / CF::G, CF::HELP)), dim3(64 * CF::W), CF::LDS, s, a);
     return hip_check(c, hipGetLastError(), "launch br_fft");
 }
 
@@ -1247,16 +1270,14 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     a.bg_bits = (int)c->p.bg_bits;
     // The ciphertexts per workgroup follow the batch, so that every one is
     // resident if it can be.  At N = 1024, q = 32, on 256 CUs: one (8 waves) up
-    // to a ciphertext per CU (2.9 ms at l = 3), two of the same up to two per CU
-    // (512: 4.7 ms), two in 4 waves, three workgroups per CU, up to six per CU
+    // to a ciphertext per CU (2.7 ms at l = 3), two of the same up to two per CU
+    // (512: 4.4 ms), two in 4 waves, three workgroups per CU, up to six per CU
     // (1024: 9.1 ms, 1500: 13.1 ms; four per workgroup 9.7 and 15.5 ms), above
     // that four in 4 waves, two workgroups per CU, whose key reads serve four
     // (4096: 29.7 ms; 31.4 ms at two).  The gadget levels of the named parameter
-    // sets (l = 3 at 32-bit words, 4 at 64-bit) are compile-time where a ring of
-    // key values is held across a transform: loaded under conditions, the
-    // compiler spilled it to scratch (64 ciphertexts 3.4 -> 2.9 ms; N = 2048,
-    // q = 64, 256 ciphertexts 15.4 -> 13.4 ms).  Any other l loads each
-    // polynomial's values when they are needed.
+    // sets (l = 3 at 32-bit words, 4 at 64-bit) are compile-time where the ring
+    // holds several polynomials: one ciphertext takes 2.66 ms, 2.88 with l a
+    // run-time value, and 512 4.39 and 4.76.
     const int l = (int)c->p.l;
     const uint32_t cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
     if (c->p.N == 256) {
@@ -1265,17 +1286,17 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
         if (l != 2) return launch_small<1, 0, false, 3>(c, a, s);
         return B <= 12 * cus ? launch_small<1, 2, true, 2>(c, a, s) : launch_small<2, 2, false, 2>(c, a, s);
     }
-    //                                                       T         R   W  G  L  KD KX twiddles AFTER WPE
+    //                                                       T         R   W  G  L  KD twiddles WPE
     if (c->q == 32) {
-        if (c->p.N == 2048) return l == 3 ? launch_fft_t<Cfg<uint32_t, 16, 8, 1, 3, 2, 1, TW_LDS, true>>(c, a, s)
-                                          : launch_fft_t<Cfg<uint32_t, 16, 8, 1, 0, 1, 0, TW_LDS, true>>(c, a, s);
-        if (B > 6 * cus) return launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, 0, TW_LDS, false>>(c, a, s);
-        if (B > 2 * cus) return launch_fft_t<Cfg<uint32_t, 8, 4, 2, 0, 1, 0, TW_LDS, false, 3>>(c, a, s);
-        if (l != 3) return launch_fft_t<Cfg<uint32_t, 8, 8, 1, 0, 2, 0, TW_REG, false>>(c, a, s);
-        return B > cus ? launch_fft_t<Cfg<uint32_t, 8, 8, 2, 3, 4, 4, TW_REG, false>>(c, a, s)
-                       : launch_fft_t<Cfg<uint32_t, 8, 8, 1, 3, 8, 8, TW_REG, true>>(c, a, s);
+        if (c->p.N == 2048) return l == 3 ? launch_fft_t<Cfg<uint32_t, 16, 8, 1, 3, 2, TW_LDS>>(c, a, s)
+                                          : launch_fft_t<Cfg<uint32_t, 16, 8, 1, 0, 1, TW_LDS>>(c, a, s);
+        if (B > 6 * cus) return launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, TW_LDS>>(c, a, s);
+        if (B > 2 * cus) return launch_fft_t<Cfg<uint32_t, 8, 4, 2, 0, 1, TW_LDS, 3>>(c, a, s);
+        if (l != 3) return launch_fft_t<Cfg<uint32_t, 8, 8, 1, 0, 2, TW_REG>>(c, a, s);
+        return B > cus ? launch_fft_t<Cfg<uint32_t, 8, 8, 2, 3, 4, TW_REG>>(c, a, s)
+                       : launch_fft_t<Cfg<uint32_t, 8, 8, 1, 3, 8, TW_REG>>(c, a, s);
     }
-    if (c->p.N == 2048) return l == 4 ? launch_fft_t<Cfg<uint64_t, 16, 8, 1, 4, 2, 1, TW_GLOBAL, true>>(c, a, s)
-                                      : launch_fft_t<Cfg<uint64_t, 16, 8, 1, 0, 1, 0, TW_GLOBAL, true>>(c, a, s);
-    return launch_fft_t<Cfg<uint64_t, 8, 8, 1, 0, 4, 0, TW_REG, false>>(c, a, s);
+    if (c->p.N == 2048) return l == 4 ? launch_fft_t<Cfg<uint64_t, 16, 8, 1, 4, 2, TW_GLOBAL>>(c, a, s)
+                                      : launch_fft_t<Cfg<uint64_t, 16, 8, 1, 0, 1, TW_GLOBAL>>(c, a, s);
+    return launch_fft_t<Cfg<uint64_t, 8, 8, 1, 0, 4, TW_REG>>(c, a, s);
 }

@@ -162,3 +162,22 @@ def test_small_ring_batches_on_both_sides_of_the_rule(l, bg):
         torch.cuda.synchronize()
         assert torch.equal(got, ref[:B]), B
     ctx.close()
+
+
+@pytest.mark.parametrize("q,N,l,bg", [(32, 1024, 3, 7), (32, 1024, 5, 6), (32, 2048, 3, 8), (64, 1024, 4, 6),
+                                      (64, 2048, 4, 6), (64, 2048, 2, 8)])
+def test_batches_that_are_topped_up_with_copies(q, N, l, bg):
+    """Batches below the smallest launch are topped up with workgroups that work
+    on a ciphertext again and store nothing: around that size every row has the
+    int8 path's bits and the memory behind the outputs keeps its own."""
+    p = si.Params(f"c{q}_{N}", q, 7, 1, N, bg, l, 2, 8, 20, 25)
+    ctx = fs.Context(p, si.torus(13, 81, p.bsk_words(), q), np.zeros(p.ksk_words(), dtype=np.uint64))
+    d = to_dev(p, si.torus(14, 82, 70 * (p.n + 1), q).reshape(70, p.n + 1))
+    _, ref = both_paths(p, ctx, d)
+    for B in (1, 7, 15, 16, 17, 31, 63, 64, 65):
+        say("copies", q, N, l, bg, "B =", B)
+        buf = torch.full((70, p.N + 1), -7, dtype=d.dtype, device=d.device)
+        ctx.tfhe_bootstrap_batch(d[:B].contiguous(), buf[:B])
+        torch.cuda.synchronize()
+        assert torch.equal(buf[:B], ref[:B]) and bool((buf[B:] == -7).all()), B
+    ctx.close()
