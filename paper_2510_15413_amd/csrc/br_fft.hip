@@ -1271,13 +1271,18 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     // The ciphertexts per workgroup follow the batch, so that every one is
     // resident if it can be.  At N = 1024, q = 32, on 256 CUs: one (8 waves) up
     // to a ciphertext per CU (2.7 ms at l = 3), two of the same up to two per CU
-    // (512: 4.4 ms), two in 4 waves, three workgroups per CU, up to six per CU
-    // (1024: 9.1 ms, 1500: 13.1 ms; four per workgroup 9.7 and 15.5 ms), above
-    // that four in 4 waves, two workgroups per CU, whose key reads serve four
-    // (4096: 29.7 ms; 31.4 ms at two).  The gadget levels of the named parameter
-    // sets (l = 3 at 32-bit words, 4 at 64-bit) are compile-time where the ring
-    // holds several polynomials: one ciphertext takes 2.66 ms, 2.88 with l a
-    // run-time value, and 512 4.39 and 4.76.
+    // (512: 4.4 ms) and in up to three rounds of those (1024: 8.8 ms, 1500: 13.1
+    // ms; four in 4 waves 9.7 and 15.5), above that four in 4 waves, two
+    // workgroups per CU, whose key reads serve four (2048: 15.1 ms, 17.5 in pairs;
+    // 4096: 29.7 ms).  A batch goes out in up to two launches where its last round
+    // would be nearly empty: 700 as 512 in pairs and 188 (9.0 -> 7.2 ms), 1100
+    // 13.5 -> 11.9, 2300 as 2048 by fours and 252 (24.6 -> 18.5); over two per CU
+    // left, the fours of the last round share a CU less and are as fast (3000:
+    // 23.4 ms, 24.4 in parts).  At another l, two in 4 waves, three workgroups per
+    // CU, stand for the pairs (l = 4: 1500 16.5 ms).
+    // The gadget levels of the named parameter sets (l = 3 at 32-bit words, 4 at
+    // 64-bit) are compile-time where the ring holds several polynomials: one
+    // ciphertext takes 2.66 ms, 2.88 with l a run-time value, and 512 4.39 and 4.76.
     const int l = (int)c->p.l;
     const uint32_t cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
     if (c->p.N == 256) {
@@ -1290,11 +1295,25 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     if (c->q == 32) {
         if (c->p.N == 2048) return l == 3 ? launch_fft_t<Cfg<uint32_t, 16, 8, 1, 3, 2, TW_LDS>>(c, a, s)
                                           : launch_fft_t<Cfg<uint32_t, 16, 8, 1, 0, 1, TW_LDS>>(c, a, s);
-        if (B > 6 * cus) return launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, TW_LDS>>(c, a, s);
-        if (B > 2 * cus) return launch_fft_t<Cfg<uint32_t, 8, 4, 2, 0, 1, TW_LDS, 3>>(c, a, s);
-        if (l != 3) return launch_fft_t<Cfg<uint32_t, 8, 8, 1, 0, 2, TW_REG>>(c, a, s);
-        return B > cus ? launch_fft_t<Cfg<uint32_t, 8, 8, 2, 3, 4, TW_REG>>(c, a, s)
-                       : launch_fft_t<Cfg<uint32_t, 8, 8, 1, 3, 8, TW_REG>>(c, a, s);
+        uint32_t done = 0;
+        const auto part = [&](uint32_t count, int (*launch)(tfhe_ctx*, const FftArgs&, hipStream_t)) {
+            FftArgs p = a;
+            p.lwe = (const uint32_t*)a.lwe + (size_t)done * (a.n + 1);
+            if (a.tv_index) p.tv_index = a.tv_index + done;
+            p.out = (uint32_t*)a.out + (size_t)done * (c->p.N + 1);
+            p.B = (int)count;
+            done += count;
+            return count ? launch(c, p, s) : TFHE_OK;
+        };
+        const uint32_t fours = B % (8 * cus) > (B < 8 * cus ? 6 : 2) * cus ? B : B - B % (8 * cus);
+        int rc = part(fours, launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, TW_LDS>>);
+        const uint32_t rest = B - done;
+        if (rc || !rest) return rc;
+        if (l != 3) return rest > 2 * cus ? part(rest, launch_fft_t<Cfg<uint32_t, 8, 4, 2, 0, 1, TW_LDS, 3>>)
+                                          : part(rest, launch_fft_t<Cfg<uint32_t, 8, 8, 1, 0, 2, TW_REG>>);
+        const uint32_t pairs = rest % (2 * cus) > cus ? rest : rest - rest % (2 * cus);
+        rc = part(pairs, launch_fft_t<Cfg<uint32_t, 8, 8, 2, 3, 4, TW_REG>>);
+        return rc ? rc : part(B - done, launch_fft_t<Cfg<uint32_t, 8, 8, 1, 3, 8, TW_REG>>);
     }
     if (c->p.N == 2048) return l == 4 ? launch_fft_t<Cfg<uint64_t, 16, 8, 1, 4, 2, TW_GLOBAL>>(c, a, s)
                                       : launch_fft_t<Cfg<uint64_t, 16, 8, 1, 0, 1, TW_GLOBAL>>(c, a, s);
