@@ -42,8 +42,8 @@
 // What it is for: the dense Toeplitz product on the int8 matrix cores ran at
 // 72% of their peak but needs 2N (k+1)l N limbs operations where the
 // transforms need about 1/100 of them.  Measured, int8 path -> this one,
-// identical bits: n = 630, N = 1024, l = 3, q = 32: 1 ciphertext 8.4 -> 2.66 ms,
-// 256 30.8 -> 2.70 ms, 1024 50 -> 9.1 ms, 4096 77 -> 30.5 ms; n = 750, N = 2048,
+// identical bits: n = 630, N = 1024, l = 3, q = 32: 1 ciphertext 8.4 -> 2.50 ms,
+// 256 30.8 -> 2.53 ms, 1024 50 -> 8.8 ms, 4096 77 -> 29.8 ms; n = 750, N = 2048,
 // l = 4, q = 64: 1 ciphertext 34 -> 10.7 ms, 256 158 -> 10.6 ms, 1000 355 -> 42.6 ms.
 //
 // What bounds it: double-precision vector issue (about 4200 vector
@@ -52,11 +52,11 @@
 // busy in a launch of 2048) and the LDS exchanges beside it; for one ciphertext
 // per workgroup the chain of a step (digits, transform, products, transform
 // back, three barriers) and the key reads (64 bytes per cycle and CU: 3100 of
-// the 10,000 cycles of a step at N = 1024, 12,300 of 33,000 at N = 2048, q = 64,
+// the 9300 cycles of a step at N = 1024, 12,300 of 33,000 at N = 2048, q = 64,
 // l = 4), which find their lines in L2: the workgroups of an XCD ask for a
 // step's lines together, each a share, while they transform the step before
 // back.  Values of the next step held in registers across its transforms, as
-// before that, cost more than the L2 hits do now (B = 1 2.87 ms).
+// before that, cost more than the L2 hits do now (B = 1 2.87 ms, against 2.66).
 #include <algorithm>
 #include <cmath>
 
@@ -519,9 +519,9 @@ struct Cfg {
     // Held by lane AHEAD at a time by waves W/2.., a step's lines need HELP
     // workgroups, 8 XCDs' worth; a smaller batch is topped up with copies.
     // Without the lines, B = 1 took 3.07 ms (3.62 with the key in HBM), at N =
-    // 2048, q = 64 15.5 ms; without copies 2.98 (3.33) and 13.8; now 2.65 (2.64)
-    // and 10.7 (at 16 copies 13.0, at 32 11.5, at 128 10.6).
-    static constexpr int HELP = W == 8 && G == 1 ? (R == 8 ? 16 : 64) : 0;
+    // 2048, q = 64 15.5 ms; with lines and 16 workgroups 2.87 and 13.0; now 2.50
+    // and 10.7 (64 and 128 workgroups: 2.52 and 2.53; 32 and 128: 11.7 and 10.7).
+    static constexpr int HELP = W == 8 && G == 1 ? (R == 8 ? 32 : 64) : 0;
     static constexpr int LINES = 2 * (L ? L : Limb<T>::COUNT + 1) * 2 * Limb<T>::COUNT * P::M / 8;
     static constexpr int AHEAD = W < 8 ? 0 : HELP ? (LINES + HELP / 8 * 256 - 1) / (HELP / 8 * 256) : 1;
     static constexpr uint32_t BUF = P::M * 16;                            // bytes of a wave's buffer
@@ -654,7 +654,21 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
         for (int t = 0; t < AHEAD; t++) __asm__ volatile("" ::"v"(line[t]));
     };
 
+    // Where the ring holds a whole step (one ciphertext, l = 3), the waves that
+    // have no output to transform back load the next step's values meanwhile: the
+    // loads of a step take 3000 cycles of the CU's path to L2, 800 of them after
+    // the last transform otherwise (64 ciphertexts 2.67 -> 2.51 ms).  The other
+    // waves have none to spare: issuing loads holds up their transforms (all
+    // loads ahead of the transforms: 3.1 ms).
+    constexpr bool EARLY = CF::L && 2 * CF::L <= KD && IR == 1 && PPR > OUT;
+    auto key_step = [&](int i) {
+#pragma unroll
+        for (int pp = 0; pp < KD; pp++)
+            if (pp < NB) key_load(kv[pp], i, pp);
+    };
+
     int abv = 0;  // abar of steps 64 (i/64) + lane
+    if (EARLY && pq0 >= OUT) key_step(0);
     lds_barrier();
     for (int i = 0; i < n; i++) {
         if ((i & 63) == 0) abv = live && i + lane < n ? (int)mod_switch<T>(lwe[i + lane], LN + 1) : 0;
@@ -724,9 +738,10 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
                 }
                 if (q0 == 0) lines_arrived();
                 __builtin_amdgcn_sched_barrier(0);  // (not earlier: the transform needs the registers)
+                if (!EARLY || pq0 < OUT)
 #pragma unroll
-                for (int pp = 0; pp < KD; pp++)
-                    if (q0 + pp < NB) key_load(kv[pp], i, q0 + pp);
+                    for (int pp = 0; pp < KD; pp++)
+                        if (q0 + pp < NB) key_load(kv[pp], i, q0 + pp);
                 lds_barrier();
 #pragma unroll
                 for (int pp = 0; pp < PPR; pp++) {
@@ -761,7 +776,8 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
             double re[R], im[R];
             typename WF::Twiddles tw;
             f.request(tw);
-            if (rd == 0) request_lines(i + 1);
+            if (EARLY && pq0 >= OUT) key_step(i + 1 < n ? i + 1 : 0);
+            if (rd == 0) request_lines(i + (EARLY ? 2 : 1));
             if (mine) f.inverse_to_first(re, im, tw);
             if (rd + 1 < IR) lds_barrier();
             if (mine) {
@@ -1270,19 +1286,19 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     a.bg_bits = (int)c->p.bg_bits;
     // The ciphertexts per workgroup follow the batch, so that every one is
     // resident if it can be.  At N = 1024, q = 32, on 256 CUs: one (8 waves) up
-    // to a ciphertext per CU (2.7 ms at l = 3), two of the same up to two per CU
+    // to a ciphertext per CU (2.5 ms at l = 3), two of the same up to two per CU
     // (512: 4.4 ms) and in up to three rounds of those (1024: 8.8 ms, 1500: 13.1
     // ms; four in 4 waves 9.7 and 15.5), above that four in 4 waves, two
     // workgroups per CU, whose key reads serve four (2048: 15.1 ms, 17.5 in pairs;
     // 4096: 29.7 ms).  A batch goes out in up to two launches where its last round
-    // would be nearly empty: 700 as 512 in pairs and 188 (9.0 -> 7.2 ms), 1100
-    // 13.5 -> 11.9, 2300 as 2048 by fours and 252 (24.6 -> 18.5); over two per CU
+    // would be nearly empty: 700 as 512 in pairs and 188 (9.1 -> 7.0 ms), 1100
+    // 13.1 -> 11.5, 2300 as 2048 by fours and 252 (24.3 -> 18.1); over two per CU
     // left, the fours of the last round share a CU less and are as fast (3000:
     // 23.4 ms, 24.4 in parts).  At another l, two in 4 waves, three workgroups per
     // CU, stand for the pairs (l = 4: 1500 16.5 ms).
     // The gadget levels of the named parameter sets (l = 3 at 32-bit words, 4 at
     // 64-bit) are compile-time where the ring holds several polynomials: one
-    // ciphertext takes 2.66 ms, 2.88 with l a run-time value, and 512 4.39 and 4.76.
+    // ciphertext took 2.66 ms, 2.88 with l a run-time value, and 512 4.39 and 4.76.
     const int l = (int)c->p.l;
     const uint32_t cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
     if (c->p.N == 256) {
