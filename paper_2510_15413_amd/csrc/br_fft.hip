@@ -815,47 +815,42 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
 // transforms 4 polynomials at a time: the digits of a ciphertext (l = 2: all of
 // them), or its 4 outputs on the way back.  Radix 8, an exchange, radix 8, and
 // the last level in the lane that multiplies (64 pairs, a lane each).  A wave
-// needs no other: no barrier, one wave per workgroup, G ciphertexts per wave
-// that share the key values it reads.
+// needs no other: no barrier, one wave per workgroup and ciphertext.
 //
-// Bounded by double-precision issue (530 of about 780 vector instructions per
-// ciphertext and step).  Measured at n = 64, l = 2 against the int8 kernel
-// (whose workgroup runs 16 ciphertexts, so that its time goes in steps of 16
-// per CU): 1 ciphertext 0.447 -> 0.144 ms, 1024 0.467 -> 0.200 ms, 2597
-// 0.489 -> 0.398 ms, 5903 0.844 -> 0.726 ms; 8192 0.896 against 0.934 ms and
-// 65,536 6.74 against 6.96 ms, where the int8 kernel stays (small_pays).
+// Bounded by its chain while a SIMD has fewer than three waves (a step of one
+// alone takes 4900 cycles, of twelve on a CU 14,800), then by double-precision
+// issue (530 of about 780 vector instructions per ciphertext and step).
+// Measured at n = 64, l = 2 against the int8 kernel (whose workgroup runs 16
+// ciphertexts, so that its time goes in steps of 16 per CU): 1 ciphertext 0.447
+// -> 0.131 ms, 1024 0.467 -> 0.183 ms, 2597 0.454 -> 0.372 ms, 5904 0.775 ->
+// 0.715 ms; 8192 0.886 against 0.960 ms and 65,536 6.74 against 7.6 ms, where
+// the int8 kernel stays (small_pays).  All of a step's key values a step ahead
+// with two waves per SIMD: 4250 0.604 ms against 0.575; two ciphertexts per wave
+// 0.687, 65,536 7.4.
 struct Small {
     static constexpr int N = 256, M = 128;
     static constexpr int T4 = 32, TN = 32 + 64;  // twiddle table: [8 blocks][4], [64 pairs]
 };
 
-template <int G>
-constexpr uint32_t small_lds() { return G * (4 * Small::M * 16 + 2 * Small::N * 4); }
-
-// L: gadget levels when compile-time (then all of a step's key values are
-// requested a step ahead when AHEAD), else 0.
-template <int G, int L, bool AHEAD, int WPE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void br_fft256_kernel(FftArgs a) {
+// L: gadget levels when compile-time (then a polynomial's key values are
+// requested while the one before is multiplied, the first one's ahead of the
+// last pass forward), else 0.
+template <int L>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3, 3))) void br_fft256_kernel(FftArgs a) {
     using T = uint32_t;
     constexpr int N = Small::N, M = Small::M, LN = 8, OUT = 4;
-    constexpr int KD = AHEAD ? 4 : 1;
-    static_assert(!AHEAD || (L > 0 && 2 * L <= 4), "key values of one pass");
+    constexpr int KD = L ? 2 : 1;
     const int lane = threadIdx.x;
     const int n = a.n, l = L ? L : a.l, NB = 2 * l;
-    const int ct0 = blockIdx.x * G;
-    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
-    d2* const bufs = (d2*)smem;                       // [G][4 polynomials][M]
-    T* const accs = (T*)(smem + G * 4 * M * 16);      // [G][2][N]
+    __shared__ d2 buf[4 * M];  // [polynomial][M]
+    __shared__ T accs[2 * N];
+    const T* const lwe = (const T*)a.lwe + (size_t)blockIdx.x * (n + 1);
 
-    for (int idx = lane; idx < G * N; idx += 64) {
-        const int c = idx / N, j = idx & (N - 1);
-        const int gi = min(ct0 + c, a.B - 1);
-        const T* lwe = (const T*)a.lwe + (size_t)gi * (n + 1);
-        const int bb = (int)mod_switch<T>(lwe[n], LN + 1);
-        const T* tv = (const T*)a.tv + (size_t)(a.tv_index ? a.tv_index[gi] : 0) * N;
-        accs[c * 2 * N + j] = 0;
-        accs[c * 2 * N + N + j] =
-            monomial_coef<T>([&](int s) -> T { return tv[s]; }, N, (2 * N - bb) & (2 * N - 1), j);
+    const int bb = (int)mod_switch<T>(lwe[n], LN + 1);
+    const T* tv = (const T*)a.tv + (size_t)(a.tv_index ? a.tv_index[blockIdx.x] : 0) * N;
+    for (int j = lane; j < N; j += 64) {
+        accs[j] = 0;
+        accs[N + j] = monomial_coef<T>([&](int s) -> T { return tv[s]; }, N, (2 * N - bb) & (2 * N - 1), j);
     }
 
     // lane: polynomial pl of the pass; point j4 (of 16) or block k, member b0
@@ -888,155 +883,128 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) 
 #pragma unroll
             for (int e = 0; e < 2; e++) v[o][e] = kp[o * M + e * 64];
     };
-    if constexpr (AHEAD) {
-#pragma unroll
-        for (int pp = 0; pp < 2 * L; pp++) key_load(kv[pp], 0, pp);
-    }
-
-    int abv[G];
+    int abv = 0;  // abar of steps 64 (i/64) + lane
     wave_order();
     for (int i = 0; i < n; i++) {
-        if ((i & 63) == 0) {
+        if ((i & 63) == 0) abv = i + lane < n ? (int)mod_switch<T>(lwe[i + lane], LN + 1) : 0;
+        const int ab = __builtin_amdgcn_readlane(abv, i & 63);
+        double ar[OUT][2], ai[OUT][2];
 #pragma unroll
-            for (int c = 0; c < G; c++)
-                abv[c] = i + lane < n ? (int)mod_switch<T>(
-                                            ((const T*)a.lwe)[(size_t)min(ct0 + c, a.B - 1) * (n + 1) + i + lane], LN + 1)
-                                      : 0;
-        }
-        double ar[G][OUT][2], ai[G][OUT][2];
+        for (int o = 0; o < OUT; o++)
 #pragma unroll
-        for (int c = 0; c < G; c++)
-#pragma unroll
-            for (int o = 0; o < OUT; o++)
-#pragma unroll
-                for (int e = 0; e < 2; e++) ar[c][o][e] = ai[c][o][e] = 0;
+            for (int e = 0; e < 2; e++) ar[o][e] = ai[o][e] = 0;
         for (int q0 = 0; q0 < NB; q0 += 4) {
             // digits and transforms of polynomials q0 .. q0 + 3 (a lane's past
             // the last one repeats it; it is not read)
             const int pq = min(q0 + pl, NB - 1), u = pq >= l ? 1 : 0;
             const int pos = shr + (l - 1 - (pq - u * l)) * bgb;
+            const T* acc = accs + u * N;
+            // digit word of coefficient 16 r + x0
+            int x0 = L == 2 ? j4 + (pl & 1) * M : j4;
+            __asm__ volatile("" : "+v"(x0));
+            const T* own = acc + x0;
+            x0 -= ab;
+            auto word = [&](int r) -> int {
+                const int x = x0 + 16 * r;
+                const T v = acc[x & (N - 1)];
+                const T m = (T)(int32_t)__builtin_amdgcn_sbfe(x, LN, 1);
+                return (int)(((C - own[16 * r]) + ((v ^ m) - m)) ^ F);
+            };
+            double re[8], im[8];
 #pragma unroll
-            for (int c = 0; c < G; c++) {
-                const int ab = __builtin_amdgcn_readlane(abv[c], i & 63);
-                const T* acc = accs + (c * 2 + u) * N;
-                // digit word of coefficient 16 r + x0
-                int x0 = L == 2 ? j4 + (pl & 1) * M : j4;
-                __asm__ volatile("" : "+v"(x0));
-                const T* own = acc + x0;
-                x0 -= ab;
-                auto word = [&](int r) -> int {
-                    const int x = x0 + 16 * r;
-                    const T v = acc[x & (N - 1)];
-                    const T m = (T)(int32_t)__builtin_amdgcn_sbfe(x, LN, 1);
-                    return (int)(((C - own[16 * r]) + ((v ^ m) - m)) ^ F);
-                };
-                double re[8], im[8];
-#pragma unroll
-                for (int r = 0; r < 8; r++) {
-                    int zr, zi;
-                    if constexpr (L == 2) {
-                        // the two levels of a component (lane rows 2u, 2u + 1)
-                        // form a half of its words each and swap copies
-                        const int z = word(r);
-                        const auto zz = __builtin_amdgcn_permlane16_swap(z, z, false, false);
-                        zr = (int)zz[0];
-                        zi = (int)zz[1];
-                    } else {
-                        zr = word(r);
-                        zi = word(r + 8);
-                    }
-                    re[r] = (double)(int)__builtin_amdgcn_sbfe(zr, pos, bgb);
-                    im[r] = (double)(int)__builtin_amdgcn_sbfe(zi, pos, bgb);
+            for (int r = 0; r < 8; r++) {
+                int zr, zi;
+                if constexpr (L == 2) {
+                    // the two levels of a component (lane rows 2u, 2u + 1)
+                    // form a half of its words each and swap copies
+                    const int z = word(r);
+                    const auto zz = __builtin_amdgcn_permlane16_swap(z, z, false, false);
+                    zr = (int)zz[0];
+                    zi = (int)zz[1];
+                } else {
+                    zr = word(r);
+                    zi = word(r + 8);
                 }
-                d2* buf = bufs + c * 4 * M;
-                lane_fwd<8>(re, im, kC1, kT1);
-#pragma unroll
-                for (int r = 0; r < 8; r++) buf[(wr ^ (2 * r)) + r * 16] = d2{re[r], im[r]};
-                wave_order();
-#pragma unroll
-                for (int r = 0; r < 8; r++) {
-                    const d2 v = buf[rd ^ (2 * r)];
-                    re[r] = v.x;
-                    im[r] = v.y;
-                }
-                lane_fwd<8>(re, im, c2, t2);
-                wave_order();
-#pragma unroll
-                for (int r = 0; r < 8; r++) buf[pr + r * 8] = d2{re[r], im[r]};
+                re[r] = (double)(int)__builtin_amdgcn_sbfe(zr, pos, bgb);
+                im[r] = (double)(int)__builtin_amdgcn_sbfe(zi, pos, bgb);
             }
+            lane_fwd<8>(re, im, kC1, kT1);
+#pragma unroll
+            for (int r = 0; r < 8; r++) buf[(wr ^ (2 * r)) + r * 16] = d2{re[r], im[r]};
+            wave_order();
+#pragma unroll
+            for (int r = 0; r < 8; r++) {
+                const d2 v = buf[rd ^ (2 * r)];
+                re[r] = v.x;
+                im[r] = v.y;
+            }
+            if (KD == 2) key_load(kv[0], i, 0);
+            lane_fwd<8>(re, im, c2, t2);
+            wave_order();
+#pragma unroll
+            for (int r = 0; r < 8; r++) buf[pr + r * 8] = d2{re[r], im[r]};
             wave_order();
 #pragma unroll
             for (int pp = 0; pp < 4; pp++) {
                 if (L ? pp >= 2 * L : q0 + pp >= NB) break;
-                if (!AHEAD) key_load(kv[0], i, q0 + pp);
+                if (KD == 1) key_load(kv[0], i, q0 + pp);
+                if (KD == 2 && pp + 1 < 2 * L) key_load(kv[(pp + 1) % KD], i, pp + 1);
+                const d2 x = buf[pp * M + lane], y = buf[pp * M + 64 + (lane ^ 4)];
+                double dr[2] = {x.x, y.x}, di[2] = {x.y, y.y};
+                bf_fwd<false>(dr[0], di[0], dr[1], di[1], w4.x, w4.y);
 #pragma unroll
-                for (int c = 0; c < G; c++) {
-                    const d2 x = bufs[(c * 4 + pp) * M + lane], y = bufs[(c * 4 + pp) * M + 64 + (lane ^ 4)];
-                    double dr[2] = {x.x, y.x}, di[2] = {x.y, y.y};
-                    bf_fwd<false>(dr[0], di[0], dr[1], di[1], w4.x, w4.y);
+                for (int o = 0; o < OUT; o++)
 #pragma unroll
-                    for (int o = 0; o < OUT; o++)
-#pragma unroll
-                        for (int e = 0; e < 2; e++) {
-                            const d2 w = kv[pp % KD][o][e];
-                            ar[c][o][e] = __builtin_fma(dr[e], w.x, ar[c][o][e]);
-                            ai[c][o][e] = __builtin_fma(dr[e], w.y, ai[c][o][e]);
-                            ar[c][o][e] = __builtin_fma(-di[e], w.y, ar[c][o][e]);
-                            ai[c][o][e] = __builtin_fma(di[e], w.x, ai[c][o][e]);
-                        }
-                }
-                if constexpr (AHEAD) key_load(kv[pp], i + 1 < n ? i + 1 : i, pp);
+                    for (int e = 0; e < 2; e++) {
+                        const d2 w = kv[pp % KD][o][e];
+                        ar[o][e] = __builtin_fma(dr[e], w.x, ar[o][e]);
+                        ai[o][e] = __builtin_fma(dr[e], w.y, ai[o][e]);
+                        ar[o][e] = __builtin_fma(-di[e], w.y, ar[o][e]);
+                        ai[o][e] = __builtin_fma(di[e], w.x, ai[o][e]);
+                    }
             }
             wave_order();
         }
         // back: the lanes of group pl transform output pl (component pl / 2, limb pl % 2)
 #pragma unroll
-        for (int c = 0; c < G; c++) {
-            d2* buf = bufs + c * 4 * M;
+        for (int o = 0; o < OUT; o++) {
+            bf_inv<false>(ar[o][0], ai[o][0], ar[o][1], ai[o][1], w4.x, w4.y);
+            buf[o * M + lane] = d2{ar[o][0], ai[o][0]};
+            buf[o * M + 64 + (lane ^ 4)] = d2{ar[o][1], ai[o][1]};
+        }
+        wave_order();
+        double re[8], im[8];
 #pragma unroll
-            for (int o = 0; o < OUT; o++) {
-                bf_inv<false>(ar[c][o][0], ai[c][o][0], ar[c][o][1], ai[c][o][1], w4.x, w4.y);
-                buf[o * M + lane] = d2{ar[c][o][0], ai[c][o][0]};
-                buf[o * M + 64 + (lane ^ 4)] = d2{ar[c][o][1], ai[c][o][1]};
-            }
-            wave_order();
-            double re[8], im[8];
+        for (int r = 0; r < 8; r++) {
+            const d2 v = buf[pr + r * 8];
+            re[r] = v.x;
+            im[r] = v.y;
+        }
+        lane_inv<8>(re, im, c2, t2);
+        wave_order();
 #pragma unroll
-            for (int r = 0; r < 8; r++) {
-                const d2 v = buf[pr + r * 8];
-                re[r] = v.x;
-                im[r] = v.y;
-            }
-            lane_inv<8>(re, im, c2, t2);
-            wave_order();
+        for (int r = 0; r < 8; r++) buf[rd ^ (2 * r)] = d2{re[r], im[r]};
+        wave_order();
 #pragma unroll
-            for (int r = 0; r < 8; r++) buf[rd ^ (2 * r)] = d2{re[r], im[r]};
-            wave_order();
+        for (int r = 0; r < 8; r++) {
+            const d2 v = buf[(wr ^ (2 * r)) + r * 16];
+            re[r] = v.x;
+            im[r] = v.y;
+        }
+        double sc[8];
+        lane_inv_first<8>(re, im, sc);
+        T* acc = accs + (pl >> 1) * N + j4;
+        const int sh = (pl & 1) * 16;
 #pragma unroll
-            for (int r = 0; r < 8; r++) {
-                const d2 v = buf[(wr ^ (2 * r)) + r * 16];
-                re[r] = v.x;
-                im[r] = v.y;
-            }
-            double sc[8];
-            lane_inv_first<8>(re, im, sc);
-            T* acc = accs + (c * 2 + (pl >> 1)) * N + j4;
-            const int sh = (pl & 1) * 16;
-#pragma unroll
-            for (int r = 0; r < 8; r++) {
-                atomicAdd(acc + 16 * r, (T)nearest(re[r], sc[r]) << sh);
-                atomicAdd(acc + 16 * r + M, (T)nearest(im[r], sc[r]) << sh);
-            }
+        for (int r = 0; r < 8; r++) {
+            atomicAdd(acc + 16 * r, (T)nearest(re[r], sc[r]) << sh);
+            atomicAdd(acc + 16 * r + M, (T)nearest(im[r], sc[r]) << sh);
         }
         wave_order();
     }
 
-    T* out = (T*)a.out;
-    for (int c = 0; c < G && ct0 + c < a.B; c++) {
-        const T* A = accs + c * 2 * N;
-        for (int j = lane; j <= N; j += 64)
-            out[(size_t)(ct0 + c) * (N + 1) + j] = j == 0 ? A[0] : j < N ? 0 - A[N - j] : A[N];
-    }
+    T* out = (T*)a.out + (size_t)blockIdx.x * (N + 1);
+    for (int j = lane; j <= N; j += 64) out[j] = j == 0 ? accs[0] : j < N ? 0 - accs[N - j] : accs[N];
 }
 
 // Key spectra of the small ring: 16 lanes per (polynomial, limb), 4 per wave.
@@ -1089,14 +1057,6 @@ __global__ __launch_bounds__(64) void fft256_key_kernel(const uint32_t* bsk, con
         out[lane] = d2{xr * scale, xi * scale};
         out[64 + lane] = d2{yr * scale, yi * scale};
     }
-}
-
-template <int G, int L, bool AHEAD, int WPE>
-int launch_small(tfhe_ctx* c, const FftArgs& a, hipStream_t s) {
-    auto k = br_fft256_kernel<G, L, AHEAD, WPE>;
-    if (L && L != a.l) return ctx_fail(c, TFHE_EINVAL, "transform kernel of another level count");
-    hipLaunchKernelGGL(k, dim3((a.B + G - 1) / G), dim3(64), small_lds<G>(), s, a);
-    return hip_check(c, hipGetLastError(), "launch br_fft256");
 }
 
 template <typename CF>
@@ -1246,17 +1206,17 @@ int fft_setup(tfhe_ctx* c, hipStream_t s) {
 
 // The small ring's transform kernel against the int8 one: linear in the batch
 // against steps of 16 ciphertexts per CU.  At n = 64, l = 2 on 256 CUs (step
-// 4096), int8 / transform in ms: 2597 0.489 / 0.398, 4096 0.521 / 0.530, 5000
-// 0.787 / 0.735, 6700 0.84 / 0.93, 9209 1.37 / 1.16, 10,400 1.38 / 1.34, 14,100
-// 1.73 / 1.65, 17,800 2.24 / 2.09, 21,500 2.62 / 2.53, 32,768 3.57 / 3.64.  So it
-// is taken in the first three quarters of the first step and the first half
-// of the next five.  At other level counts (l = 3: 2048 0.784 / 0.489, 5: 1.21 /
-// 0.69, 1: 0.321 / 0.293) up to half a step.
+// 4096), int8 / transform in ms: 2560 0.454 / 0.404, 3072 0.447 / 0.412, 3328
+// 0.459 / 0.483, 4352 0.750 / 0.583, 6144 0.783 / 0.727, 6656 0.804 / 0.820, 9216
+// 1.32 / 1.08, 10,240 1.33 / 1.21, 14,336 1.66 / 1.64, 18,432 2.17 / 2.13, 22,528
+// 2.54 / 2.61.  So it is taken in the first three quarters of the first step and
+// the first half of the next four.  At other level counts (l = 3: 2048 0.784 /
+// 0.489, 5: 1.21 / 0.69, 1: 0.321 / 0.293) up to half a step.
 static bool small_pays(const tfhe_ctx* c, uint32_t B) {
     const uint64_t step = 16ull * (c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256);
     if (c->p.l != 2) return B <= step / 2;
     const uint64_t full = B / step, rem = B % step;
-    return full == 0 ? rem <= step * 3 / 4 : full <= 5 && rem <= step / 2 && rem > 0;
+    return full == 0 ? rem <= step * 3 / 4 : full <= 4 && rem <= step / 2 && rem > 0;
 }
 
 // Whether a batch of B takes the transform path: unless a tuning knob asks for
@@ -1302,10 +1262,8 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     const int l = (int)c->p.l;
     const uint32_t cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
     if (c->p.N == 256) {
-        // one ciphertext per wave with a step's key values requested ahead while
-        // every wave has its SIMD slot (12 per CU), two per wave above
-        if (l != 2) return launch_small<1, 0, false, 3>(c, a, s);
-        return B <= 12 * cus ? launch_small<1, 2, true, 2>(c, a, s) : launch_small<2, 2, false, 2>(c, a, s);
+        hipLaunchKernelGGL(l == 2 ? br_fft256_kernel<2> : br_fft256_kernel<0>, dim3(B), dim3(64), 0, s, a);
+        return hip_check(c, hipGetLastError(), "launch br_fft256");
     }
     //                                                       T         R   W  G  L  KD twiddles WPE
     if (c->q == 32) {
