@@ -103,11 +103,10 @@ size_t tfhe_ksk_words(const tfhe_params* p);
  * sizes in bytes must match tfhe_bsk_words/tfhe_ksk_words), builds the
  * device-only limb-planar Toeplitz form of the BSK and allocates workspace
  * lazily.  With N = 1024 or 2048, or N = 256 and torus_bits = 32, it also
- * holds the transforms of the
- * BSK's limbs (16 bytes per coefficient pair and limb: 124 MB at n = 630,
- * N = 1024, l = 3; 590 MB at n = 750, N = 2048, l = 4, torus_bits = 64), from
- * which the transform blind rotation runs; without room the int8 kernels are
- * used.  With torus_bits = 32 it also keeps the key-switching table
+ * holds the transforms of the BSK's limbs (16 bytes per coefficient pair and
+ * limb: 124 MB at n = 630, N = 1024, l = 3; 590 MB at n = 750, N = 2048, l = 4,
+ * torus_bits = 64), from which the transform blind rotation runs; without room
+ * the int8 kernels are used.  With torus_bits = 32 it also keeps the key-switching table
  * as int8 limbs (4 bytes per word, 84 MB at the standard set) for the MFMA
  * key switch; without room the key switch reads the word table.  Blocks
  * until the keys are on the device.  The context owns its copies; the

@@ -2,8 +2,8 @@
 
 The library (``libfhesql.so``, C ABI in ``include/fhesql.h``) runs the server
 hot path of FHE-SQL's oblivious selection on one GPU: TFHE gate bootstrapping
-(blind rotation with an exact limb-split int8 MFMA external product, sample
-extraction, key switching) inside the boolean circuits of the WHERE mask (one
+(blind rotation with an exact external product, by double-precision transforms
+of key limbs or limb-split int8 MFMA, sample extraction, key switching) inside the boolean circuits of the WHERE mask (one
 predicate, many tables in one batch, or a whole expression tree), the masked
 select and the masked SUM; 64-bit programmable bootstrapping over radix
 blocks; and a continuous-batching query server.  This package is its thin
