@@ -42,17 +42,17 @@
 // What it is for: the dense Toeplitz product on the int8 matrix cores ran at
 // 72% of their peak but needs 2N (k+1)l N limbs operations where the
 // transforms need about 1/100 of them.  Measured, int8 path -> this one,
-// identical bits: n = 630, N = 1024, l = 3, q = 32: 1 ciphertext 8.4 -> 2.50 ms,
-// 256 30.8 -> 2.53 ms, 1024 50 -> 8.8 ms, 4096 77 -> 29.8 ms; n = 750, N = 2048,
-// l = 4, q = 64: 1 ciphertext 34 -> 10.7 ms, 256 158 -> 10.6 ms, 1000 355 -> 42.6 ms.
+// identical bits: n = 630, N = 1024, l = 3, q = 32: 1 ciphertext 8.4 -> 2.36 ms,
+// 256 30.8 -> 2.38 ms, 1024 50 -> 8.3 ms, 4096 77 -> 29.8 ms; n = 750, N = 2048,
+// l = 4, q = 64: 1 ciphertext 34 -> 10.2 ms, 256 158 -> 10.1 ms, 1000 355 -> 40.4 ms.
 //
 // What bounds it: double-precision vector issue (about 4200 vector
 // instructions per ciphertext and step at N = 1024, l = 3, q = 32, 3000 of them
 // double precision at 4.3-4.7 cycles of their SIMD; the vector units are 61%
 // busy in a launch of 2048) and the LDS exchanges beside it; for one ciphertext
 // per workgroup the chain of a step (digits, transform, products, transform
-// back, three barriers) and the key reads (64 bytes per cycle and CU: 3100 of
-// the 9300 cycles of a step at N = 1024, 12,300 of 33,000 at N = 2048, q = 64,
+// back, five barriers) and the key reads (64 bytes per cycle and CU: 3100 of
+// the 8800 cycles of a step at N = 1024, 12,300 of 32,000 at N = 2048, q = 64,
 // l = 4), which find their lines in L2: the workgroups of an XCD ask for a
 // step's lines together, each a share, while they transform the step before
 // back.  Values of the next step held in registers across its transforms, as
@@ -527,7 +527,13 @@ struct Cfg {
     static constexpr uint32_t BUF = P::M * 16;                            // bytes of a wave's buffer
     static constexpr uint32_t ACC = W * BUF;                              // accumulators [G][2][N]
     static constexpr uint32_t TW = ACC + G * 2 * P::N * (uint32_t)sizeof(T);  // twiddles (TW_LDS)
-    static constexpr uint32_t LDS = TW + (TWS == TW_LDS ? (uint32_t)(R * F::S2 + 32 * P::NT3) * 16 : 0);
+    static constexpr uint32_t ZS = TW + (TWS == TW_LDS ? (uint32_t)(R * F::S2 + 32 * P::NT3) * 16 : 0);
+    // Digit words [G][2][N], formed once for all levels: behind the rest if LDS
+    // has room, else in the first buffers if one round reads them all.
+    static constexpr uint32_t ZBYTES = G * 2 * P::N * 4;
+    static constexpr bool ZROOM = W == 8 && ZS + ZBYTES <= 160 * 1024;
+    static constexpr bool SHARE = ZROOM || (W == 8 && L && 2 * L * G <= W);
+    static constexpr uint32_t LDS = ZS + (ZROOM ? ZBYTES : 0);
 };
 
 template <typename CF>
@@ -595,21 +601,38 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
     const T C = ((T)1 << (shr - 1)) + F;
     const int fb = Q == 32 ? shr : shr - 32;
 
-    // digit words of X^{ab} ACC_u - ACC_u at coefficients 64 r + lane, r < 2R
-    auto form = [&](uint32_t (&z)[2 * R], int u, int ab) {
+    // digit words of X^{ab} ACC_u - ACC_u at coefficients j0 + 64 r + lane, r < CNT
+    auto form_words = [&](auto& z, int u, int j0, int ab) {
+        constexpr int CNT = sizeof(z) / 4;
         const T* acc = acc_ct + (size_t)u * N;
-        int x0 = lane;
+        int x0 = j0 + lane;
         __asm__ volatile("" : "+v"(x0));
         const T* own = acc + x0;
         x0 -= ab;
 #pragma unroll
-        for (int r = 0; r < 2 * R; r++) {
+        for (int r = 0; r < CNT; r++) {
             const int x = x0 + 64 * r;
             const T v = acc[x & (N - 1)];
             const T m = (T)(int64_t)(int32_t)__builtin_amdgcn_sbfe(x, LN, 1);  // all ones: negate
             const T zz = (T)((T)(C - own[64 * r]) + (T)((v ^ m) - m)) ^ F;
             z[r] = Q == 32 ? (uint32_t)zz : (uint32_t)((uint64_t)zz >> 32);
         }
+    };
+    auto form = [&](uint32_t (&z)[2 * R], int u, int ab) { form_words(z, u, 0, ab); };
+    // SHARE: a ciphertext's waves form an equal part of its words each, once for
+    // all levels.  About 170 of a digit polynomial's 500 vector instructions were
+    // its words, formed again per level, on the SIMDs with two of a step's six
+    // transforms: 1 ciphertext 2.51 -> 2.36 ms, 512 4.41 -> 4.14; N = 2048, q = 64
+    // 10.7 -> 10.2.
+    constexpr bool SHARE = CF::SHARE;
+    uint32_t* const zs = (uint32_t*)(smem + (CF::ZROOM ? CF::ZS : 0)) + ct * 2 * N + lane;
+    auto form_share = [&](int ab) {
+        constexpr int CNT = 2 * N / (64 * PPR);
+        const int u = pq0 / (PPR / 2), j0 = pq0 % (PPR / 2) * (64 * CNT);
+        uint32_t z[CNT];
+        form_words(z, u, j0, ab);
+#pragma unroll
+        for (int r = 0; r < CNT; r++) zs[u * N + j0 + 64 * r] = z[r];
     };
     auto transform = [&](const uint32_t (&z)[2 * R], int p) {
         const int pos = fb + (l - 1 - p) * bgb;
@@ -729,13 +752,24 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
                 }
             }
         } else {
+            if constexpr (SHARE) {
+                form_share(ab);
+                lds_barrier();
+            }
             for (int q0 = 0; q0 < NB; q0 += PPR) {
-                if (q0 + pq0 < NB) {
-                    const int u = q0 + pq0 >= l;
-                    uint32_t z[2 * R];
-                    form(z, u, ab);
-                    transform(z, q0 + pq0 - u * l);
+                const bool any = q0 + pq0 < NB;
+                const int u = q0 + pq0 >= l;
+                uint32_t z[2 * R];
+                if (any) {
+                    if constexpr (SHARE) {
+#pragma unroll
+                        for (int r = 0; r < 2 * R; r++) z[r] = zs[u * N + 64 * r];
+                    } else {
+                        form(z, u, ab);
+                    }
                 }
+                if (SHARE && !CF::ZROOM) lds_barrier();  // the words lie in the buffers
+                if (any) transform(z, q0 + pq0 - u * l);
                 if (q0 == 0) lines_arrived();
                 __builtin_amdgcn_sched_barrier(0);  // (not earlier: the transform needs the registers)
                 if (!EARLY || pq0 < OUT)
@@ -1246,13 +1280,13 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     a.bg_bits = (int)c->p.bg_bits;
     // The ciphertexts per workgroup follow the batch, so that every one is
     // resident if it can be.  At N = 1024, q = 32, on 256 CUs: one (8 waves) up
-    // to a ciphertext per CU (2.5 ms at l = 3), two of the same up to two per CU
-    // (512: 4.4 ms) and in up to three rounds of those (1024: 8.8 ms, 1500: 13.1
+    // to a ciphertext per CU (2.4 ms at l = 3), two of the same up to two per CU
+    // (512: 4.1 ms) and in up to three rounds of those (1024: 8.3 ms, 1500: 12.4
     // ms; four in 4 waves 9.7 and 15.5), above that four in 4 waves, two
-    // workgroups per CU, whose key reads serve four (2048: 15.1 ms, 17.5 in pairs;
+    // workgroups per CU, whose key reads serve four (2048: 15.1 ms, 16.6 in pairs;
     // 4096: 29.7 ms).  A batch goes out in up to two launches where its last round
-    // would be nearly empty: 700 as 512 in pairs and 188 (9.1 -> 7.0 ms), 1100
-    // 13.1 -> 11.5, 2300 as 2048 by fours and 252 (24.3 -> 18.1); over two per CU
+    // would be nearly empty: 700 as 512 in pairs and 188 (9.1 -> 6.6 ms), 1100
+    // 13.1 -> 10.9, 2300 as 2048 by fours and 252 (24.3 -> 18.0); over two per CU
     // left, the fours of the last round share a CU less and are as fast (3000:
     // 23.4 ms, 24.4 in parts).  At another l, two in 4 waves, three workgroups per
     // CU, stand for the pairs (l = 4: 1500 16.5 ms).
