@@ -1281,15 +1281,16 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     // The ciphertexts per workgroup follow the batch, so that every one is
     // resident if it can be.  At N = 1024, q = 32, on 256 CUs: one (8 waves) up
     // to a ciphertext per CU (2.4 ms at l = 3), two of the same up to two per CU
-    // (512: 4.1 ms) and in up to three rounds of those (1024: 8.3 ms, 1500: 12.4
-    // ms; four in 4 waves 9.7 and 15.5), above that four in 4 waves, two
-    // workgroups per CU, whose key reads serve four (2048: 15.1 ms, 16.6 in pairs;
-    // 4096: 29.7 ms).  A batch goes out in up to two launches where its last round
-    // would be nearly empty: 700 as 512 in pairs and 188 (9.1 -> 6.6 ms), 1100
-    // 13.1 -> 10.9, 2300 as 2048 by fours and 252 (24.3 -> 18.0); over two per CU
-    // left, the fours of the last round share a CU less and are as fast (3000:
-    // 23.4 ms, 24.4 in parts).  At another l, two in 4 waves, three workgroups per
-    // CU, stand for the pairs (l = 4: 1500 16.5 ms).
+    // (512: 4.1 ms) and in rounds of those up to seven per CU (1024: 8.3 ms, 1500:
+    // 12.4, 1792: 14.8; four in 4 waves 9.7, 15.5, 15.7), above that four in 4
+    // waves, two workgroups per CU, whose key reads serve four (2048: 15.6 ms, 16.6
+    // in pairs; 4096: 29.8 ms).  A batch goes out in up to three launches where its
+    // last round would be nearly empty: 700 as 512 in pairs and 188 (9.1 -> 6.6
+    // ms), 1100 13.1 -> 10.9, 2300 as 2048 by fours and 252 (24.3 -> 18.0), 2700
+    // 23.6 -> 22.3; with more than three per CU left the fours of the last round
+    // share a CU less and are as fast (3000: 23.3 ms, 23.9 in parts).  At another
+    // l, two in 4 waves, three workgroups per CU, stand for the pairs up to six
+    // per CU (l = 4: 1500 16.5 ms), and up to two per CU are split off.
     // The gadget levels of the named parameter sets (l = 3 at 32-bit words, 4 at
     // 64-bit) are compile-time where the ring holds several polynomials: one
     // ciphertext took 2.66 ms, 2.88 with l a run-time value, and 512 4.39 and 4.76.
@@ -1313,7 +1314,8 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
             done += count;
             return count ? launch(c, p, s) : TFHE_OK;
         };
-        const uint32_t fours = B % (8 * cus) > (B < 8 * cus ? 6 : 2) * cus ? B : B - B % (8 * cus);
+        const uint32_t split = (l == 3 ? B < 8 * cus ? 7 : 3 : B < 8 * cus ? 6 : 2) * cus;
+        const uint32_t fours = B % (8 * cus) > split ? B : B - B % (8 * cus);
         int rc = part(fours, launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, TW_LDS>>);
         const uint32_t rest = B - done;
         if (rc || !rest) return rc;

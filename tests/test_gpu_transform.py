@@ -191,11 +191,11 @@ def test_batches_launched_in_parts(l, bg):
     p = si.Params("parts", 32, 5, 1, 1024, bg, l, 2, 8, 20, 25)
     ctx = fs.Context(p, si.torus(15, 83, p.bsk_words(), 32), np.zeros(p.ksk_words(), dtype=np.uint64))
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    top = 10 * cus + 3
+    top = 11 * cus + 3
     d = to_dev(p, si.torus(16, 84, 200 * (p.n + 1), 32).reshape(200, p.n + 1)).repeat(top // 200 + 1, 1)[:top].contiguous()
     ref = both_paths(p, ctx, d[:200])[1].repeat(top // 200 + 1, 1)[:top]
-    for B in (2 * cus, 2 * cus + 1, 3 * cus, 3 * cus + 1, 4 * cus + 1, 6 * cus, 6 * cus + 1, 8 * cus, 8 * cus + 1,
-              9 * cus + 1, 10 * cus, top):
+    for B in (2 * cus, 2 * cus + 1, 3 * cus, 3 * cus + 1, 4 * cus + 1, 6 * cus, 6 * cus + 1, 7 * cus, 7 * cus + 1,
+              8 * cus, 8 * cus + 1, 9 * cus + 1, 10 * cus, 10 * cus + 3, 11 * cus, top):
         say("parts", l, "B =", B)
         buf = torch.full((top, p.N + 1), -7, dtype=d.dtype, device=d.device)
         ctx.tfhe_bootstrap_batch(d[:B], buf[:B])
