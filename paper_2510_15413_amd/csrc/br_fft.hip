@@ -43,7 +43,7 @@
 // 72% of their peak but needs 2N (k+1)l N limbs operations where the
 // transforms need about 1/100 of them.  Measured, int8 path -> this one,
 // identical bits: n = 630, N = 1024, l = 3, q = 32: 1 ciphertext 8.4 -> 2.36 ms,
-// 256 30.8 -> 2.38 ms, 1024 50 -> 8.3 ms, 4096 77 -> 29.8 ms; n = 750, N = 2048,
+// 256 30.8 -> 2.38 ms, 1024 50 -> 8.3 ms, 4096 77 -> 27.7 ms; n = 750, N = 2048,
 // l = 4, q = 64: 1 ciphertext 34 -> 10.2 ms, 256 158 -> 10.1 ms, 1000 355 -> 40.4 ms.
 //
 // What bounds it: double-precision vector issue (about 4200 vector
@@ -501,7 +501,7 @@ struct FftArgs {
     const void* tv;           // test polynomials [ntv][N] words
     const int32_t* tv_index;  // [B] or null
     void* out;                // [B][N+1] words
-    int B, n, l, bg_bits;
+    int B, n, l, bg_bits, cus;
 };
 
 // One configuration: W waves and G ciphertexts per workgroup; KD: a thread's
@@ -691,11 +691,27 @@ __global__ __launch_bounds__(64 * CF::W) __attribute__((amdgpu_waves_per_eu(CF::
     };
 
     int abv = 0;  // abar of steps 64 (i/64) + lane
+    // Workgroups that share a CU start together and run their phases at the same
+    // time, one in the other's way (a launch of one round 15.5 ms, of eight
+    // rounds, where they drift apart, 14.2 per round).  So the second to come to
+    // a CU goes first for 5/8 of the steps and then the other one, so that both
+    // end together: 2048 ciphertexts 15.5 -> 13.9 ms, 4096 29.7 -> 27.7, 16,384
+    // 113.5 -> 111.0.  (1/2^k of the steps in turn: 14.9 at 1 and 16 steps, 14.6 at
+    // 256; 11/16, 3/4, 13/16, all: 13.8, 14.0, 14.4, 15.5, and 28.6 at 4096 for
+    // 11/16; three workgroups of two ciphertexts per CU: 1% slower with it.)
+    const bool second = blockIdx.x / a.cus & 1;
+    const int swap_at = n * 5 / 8;
     if (EARLY && pq0 >= OUT) key_step(0);
     lds_barrier();
     for (int i = 0; i < n; i++) {
         if ((i & 63) == 0) abv = live && i + lane < n ? (int)mod_switch<T>(lwe[i + lane], LN + 1) : 0;
         const int ab = __builtin_amdgcn_readlane(abv, i & 63);
+        if constexpr (G == 4) {
+            if (i == 0 || i == swap_at) {
+                if (second == (i == 0)) __builtin_amdgcn_s_setprio(2);
+                else __builtin_amdgcn_s_setprio(0);
+            }
+        }
         double ar[OT][2][G], ai[OT][2][G];
 #pragma unroll
         for (int o = 0; o < OT; o++)
@@ -1278,24 +1294,24 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
     a.n = (int)c->p.n;
     a.l = (int)c->p.l;
     a.bg_bits = (int)c->p.bg_bits;
+    a.cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
     // The ciphertexts per workgroup follow the batch, so that every one is
     // resident if it can be.  At N = 1024, q = 32, on 256 CUs: one (8 waves) up
     // to a ciphertext per CU (2.4 ms at l = 3), two of the same up to two per CU
-    // (512: 4.1 ms) and in rounds of those up to seven per CU (1024: 8.3 ms, 1500:
-    // 12.4, 1792: 14.8; four in 4 waves 9.7, 15.5, 15.7), above that four in 4
-    // waves, two workgroups per CU, whose key reads serve four (2048: 15.6 ms, 16.6
-    // in pairs; 4096: 29.8 ms).  A batch goes out in up to three launches where its
-    // last round would be nearly empty: 700 as 512 in pairs and 188 (9.1 -> 6.6
-    // ms), 1100 13.1 -> 10.9, 2300 as 2048 by fours and 252 (24.3 -> 18.0), 2700
-    // 23.6 -> 22.3; with more than three per CU left the fours of the last round
-    // share a CU less and are as fast (3000: 23.3 ms, 23.9 in parts).  At another
-    // l, two in 4 waves, three workgroups per CU, stand for the pairs up to six
-    // per CU (l = 4: 1500 16.5 ms), and up to two per CU are split off.
+    // (512: 4.1 ms) and in rounds of those up to six per CU (1024: 8.3 ms, 1500:
+    // 12.3; four in 4 waves 14.0), above that four in 4 waves, two workgroups per
+    // CU, whose key reads serve four (1600: 14.0 ms, 15.0 in pairs; 2048: 14.1;
+    // 4096: 27.7).  What is left after full rounds of those is launched by the
+    // same rule: 700 as 512 in pairs and 188 by ones (6.6 ms, 9.1 in one launch of
+    // two in 4 waves), 1100 10.9 (13.1), 2300 16.5 (24.3 all by fours), 2900 22.5
+    // (23.4), 3600 28.4 (30.5).  At another l, two in 4 waves, three workgroups per
+    // CU, stand for the pairs (l = 4: 1500 16.5 ms, 16.9 by fours; 2600 28.2, 28.6
+    // all by fours).
     // The gadget levels of the named parameter sets (l = 3 at 32-bit words, 4 at
     // 64-bit) are compile-time where the ring holds several polynomials: one
     // ciphertext took 2.66 ms, 2.88 with l a run-time value, and 512 4.39 and 4.76.
     const int l = (int)c->p.l;
-    const uint32_t cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
+    const uint32_t cus = (uint32_t)a.cus;
     if (c->p.N == 256) {
         hipLaunchKernelGGL(l == 2 ? br_fft256_kernel<2> : br_fft256_kernel<0>, dim3(B), dim3(64), 0, s, a);
         return hip_check(c, hipGetLastError(), "launch br_fft256");
@@ -1314,8 +1330,7 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
             done += count;
             return count ? launch(c, p, s) : TFHE_OK;
         };
-        const uint32_t split = (l == 3 ? B < 8 * cus ? 7 : 3 : B < 8 * cus ? 6 : 2) * cus;
-        const uint32_t fours = B % (8 * cus) > split ? B : B - B % (8 * cus);
+        const uint32_t fours = B % (8 * cus) > 6 * cus ? B : B - B % (8 * cus);
         int rc = part(fours, launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, TW_LDS>>);
         const uint32_t rest = B - done;
         if (rc || !rest) return rc;
