@@ -46,10 +46,10 @@
 // 256 30.8 -> 2.38 ms, 1024 50 -> 8.3 ms, 4096 77 -> 27.7 ms; n = 750, N = 2048,
 // l = 4, q = 64: 1 ciphertext 34 -> 10.2 ms, 256 158 -> 10.1 ms, 1000 355 -> 40.4 ms.
 //
-// What bounds it: double-precision vector issue (about 4200 vector
+// What bounds it: double-precision vector issue (about 4450 vector
 // instructions per ciphertext and step at N = 1024, l = 3, q = 32, 3000 of them
-// double precision at 4.3-4.7 cycles of their SIMD; the vector units are 61%
-// busy in a launch of 2048) and the LDS exchanges beside it; for one ciphertext
+// double precision at 4.3-4.7 cycles of their SIMD; the vector units are 73%
+// busy in a launch of 4096) and the LDS exchanges beside it; for one ciphertext
 // per workgroup the chain of a step (digits, transform, products, transform
 // back, five barriers) and the key reads (64 bytes per cycle and CU: 3100 of
 // the 8800 cycles of a step at N = 1024, 12,300 of 32,000 at N = 2048, q = 64,
@@ -519,8 +519,8 @@ struct Cfg {
     // Held by lane AHEAD at a time by waves W/2.., a step's lines need HELP
     // workgroups, 8 XCDs' worth; a smaller batch is topped up with copies.
     // Without the lines, B = 1 took 3.07 ms (3.62 with the key in HBM), at N =
-    // 2048, q = 64 15.5 ms; with lines and 16 workgroups 2.87 and 13.0; now 2.50
-    // and 10.7 (64 and 128 workgroups: 2.52 and 2.53; 32 and 128: 11.7 and 10.7).
+    // 2048, q = 64 15.5 ms; with lines and 16 workgroups 2.87 and 13.0, with 32
+    // 2.50 and 11.7, 64 2.52 and 10.7, 128 2.53 and 10.7.
     static constexpr int HELP = W == 8 && G == 1 ? (R == 8 ? 32 : 64) : 0;
     static constexpr int LINES = 2 * (L ? L : Limb<T>::COUNT + 1) * 2 * Limb<T>::COUNT * P::M / 8;
     static constexpr int AHEAD = W < 8 ? 0 : HELP ? (LINES + HELP / 8 * 256 - 1) / (HELP / 8 * 256) : 1;
