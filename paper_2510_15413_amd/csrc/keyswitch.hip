@@ -427,8 +427,10 @@ __global__ __launch_bounds__(THREADS) void ks_mfma_kernel(const uint32_t* __rest
 // ciphertext) are staged per barrier, so that a table read has 64 MFMAs to
 // arrive.  The table's 16-byte units lie in LDS as the lanes read them,
 // swizzled by (chunk, part) so that the 16 lanes that write one word's units
-// touch 16 slots.  Bounded by the matrix pipe and the digit words (52 vector
-// operations beside 16 MFMAs of 16 cycles).  Measured at n = 630, N = 1024, the
+// touch 16 slots.  Bounded by the table's way from L2 through LDS (16 KB per
+// workgroup for 64 MFMAs of 16 cycles a wave, with 4 KB of digits): forming the
+// digits (48 vector operations per 16 MFMAs) and reading the fragments a chunk
+// ahead, interleaved with the MFMAs, left the times as they are (4096 323 us).  Measured at n = 630, N = 1024, the
 // generic form -> this: 1 ciphertext 32 -> 25 us, 300 92 -> 63 us, 1024
 // 319 -> 111 us, 2048 451 -> 200 us, 4096 568 -> 322 us, 65,536 6.68 -> 4.55 ms.
 template <int KM_CT, bool SPLIT>
