@@ -430,9 +430,10 @@ __global__ __launch_bounds__(THREADS) void ks_mfma_kernel(const uint32_t* __rest
 // touch 16 slots.  Bounded by the table's way from L2 through LDS (16 KB per
 // workgroup for 64 MFMAs of 16 cycles a wave, with 4 KB of digits): forming the
 // digits (48 vector operations per 16 MFMAs) and reading the fragments a chunk
-// ahead, interleaved with the MFMAs, left the times as they are (4096 323 us).  Measured at n = 630, N = 1024, the
-// generic form -> this: 1 ciphertext 32 -> 25 us, 300 92 -> 63 us, 1024
-// 319 -> 111 us, 2048 451 -> 200 us, 4096 568 -> 322 us, 65,536 6.68 -> 4.55 ms.
+// ahead, interleaved with the MFMAs, left the times as they are (4096 323 us).
+// Measured at n = 630, N = 1024, the generic form -> this: 1 ciphertext 32 ->
+// 25 us, 300 92 -> 63 us, 1024 319 -> 111 us, 2048 451 -> 200 us, 4096 568 ->
+// 322 us, 65,536 6.68 -> 4.55 ms.
 template <int KM_CT, bool SPLIT>
 __global__ __launch_bounds__(THREADS) void ks_mfma8_kernel(const uint32_t* __restrict__ big,
                                                            const uint4* __restrict__ dig8v,
