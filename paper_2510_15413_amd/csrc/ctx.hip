@@ -488,7 +488,7 @@ extern "C" int tfhe_keyswitch_batch(tfhe_ctx* c, const void* d_in, void* d_out, 
     hipStream_t s = (hipStream_t)stream;
     int rc = ws_acquire(c, s, ks_digits_bytes(c, B));
     if (rc) return rc;
-    rc = launch_keyswitch(c, d_in, d_out, nullptr, B, c->ws, c->ws_bytes, s);
+    rc = launch_keyswitch(c, d_in, d_out, nullptr, nullptr, B, c->ws, c->ws_bytes, s);
     const int rr = ws_release(c, s);
     return rc ? rc : rr;
 }

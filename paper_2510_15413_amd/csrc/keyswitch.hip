@@ -33,9 +33,12 @@
 // Small batches.  A few ciphertexts fill only one group of workgroups (40 at
 // n = 630, 47 at n = 750), each with a serial chain of kN t 2^b / 64 chunks (or
 // kN coefficients) whose table reads come from HBM one after another.  So the
-// chain is cut into slices, a few per CU; a slice adds its sums to the outputs
-// with atomic adds (exact mod 2^q in any order), which the digit pre-pass has
-// set to (0^n, b').
+// chain is cut into slices, a few per CU; a slice adds its sums with atomic adds
+// (exact mod 2^q in any order) to a row per ciphertext, which the digit pre-pass
+// has set to (0^n, b').  The rows are the outputs themselves where those are one
+// array; where each ciphertext has an output address, two may have the same one
+// (the same query twice in a batch, queries over overlapping rows), so the rows
+// are then scratch and a last kernel stores them.
 #include <algorithm>
 
 #include "fhesql_internal.h"
@@ -66,17 +69,16 @@ struct Vec16<uint64_t> {
 // kN a multiple of 64), else [i][c].
 template <typename T, typename D, bool VEC = false>
 __global__ __launch_bounds__(THREADS) void ks_digits_kernel(const T* __restrict__ big, D* __restrict__ dig, int B,
-                                                            int kN, int tb, int n, T* out, const uint64_t* out_ptrs,
-                                                            int set_out) {
+                                                            int kN, int tb, int n, T* sums) {
     __shared__ uint32_t blk[64][65];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int i0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-    if (set_out) {
-        // outputs (0^n, b') of the block's ciphertexts, words split over gridDim.x blocks
+    if (sums) {
+        // (0^n, b') in the rows of the block's ciphertexts, words split over gridDim.x blocks
         const int per = (n + (int)gridDim.x) / (int)gridDim.x;
         const int k0 = blockIdx.x * per, k1 = min(k0 + per, n + 1);
         for (int c = c0 + w; c < min(c0 + 64, B); c += THREADS / 64) {
-            T* dst = out_ptrs ? (T*)(uintptr_t)out_ptrs[c] : out + (size_t)c * (n + 1);
+            T* dst = sums + (size_t)c * (n + 1);
             for (int k = k0 + lane; k < k1; k += 64) dst[k] = k == n ? big[(size_t)c * (kN + 1) + kN] : (T)0;
         }
     }
@@ -105,11 +107,30 @@ __global__ __launch_bounds__(THREADS) void ks_digits_kernel(const T* __restrict_
     }
 }
 
+// The sliced sums [B][n+1] to the ciphertexts' output addresses, a wave each.
+template <typename T>
+__global__ __launch_bounds__(THREADS) void ks_store_kernel(const T* __restrict__ sums, const uint64_t* out_ptrs, int B,
+                                                           int n) {
+    const int c = blockIdx.x * (THREADS / 64) + (threadIdx.x >> 6);
+    if (c >= B) return;
+    T* dst = (T*)(uintptr_t)out_ptrs[c];
+    for (int k = threadIdx.x & 63; k <= n; k += 64) dst[k] = sums[(size_t)c * (n + 1) + k];
+}
+
+// Where a launch puts its results: output rows, or an address per ciphertext;
+// `sums`: scratch of B rows for the sliced launches of the latter.
+template <typename T>
+struct KsOut {
+    T* out;
+    const uint64_t* ptrs;
+    T* sums;
+};
+
 struct KsPlace {
     int tiles, groups;  // word tiles and ciphertext groups
     int per;            // workgroups per XCD run (the grid is 8 * per)
     int tile_major;     // 1: runs of consecutive tiles, 0: runs of consecutive groups
-    int slices;         // slices of the sum; more than one: added to the outputs atomically
+    int slices;         // slices of the sum; more than one: added to the rows of sums atomically
 };
 
 // Slices of a sum of `steps` serial steps whose launch has `wgs` workgroups:
@@ -126,6 +147,20 @@ int ks_slices(const tfhe_ctx* c, int wgs, int steps, int per_cu, int full = 1) {
     const int cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
     if (wgs >= full * cus) return 1;
     return std::max(1, std::min(per_cu * cus / wgs, steps / 8));
+}
+
+// Rows that a launch of `slices` slices sums into (null: it stores its results itself).
+template <typename T>
+T* ks_sum_rows(const KsOut<T>& o, int slices) {
+    return slices <= 1 ? nullptr : o.ptrs ? o.sums : o.out;
+}
+
+// Stores the sums of a sliced launch that went to scratch.
+template <typename T>
+void launch_ks_store(const KsOut<T>& o, int slices, uint32_t B, int n, hipStream_t s) {
+    if (slices > 1 && o.ptrs)
+        hipLaunchKernelGGL(ks_store_kernel<T>, dim3((B + THREADS / 64 - 1) / (THREADS / 64)), dim3(THREADS), 0, s,
+                           (const T*)o.sums, o.ptrs, (int)B, n);
 }
 
 // (tile, group, slice) of a workgroup: L runs on XCD L % 8 as the (L / 8)-th
@@ -545,8 +580,7 @@ __global__ __launch_bounds__(THREADS) void ks_mfma8_kernel(const uint32_t* __res
 }
 
 template <int KM_CT>
-int launch_mfma8_ct(tfhe_ctx* c, const uint32_t* big, void* dig, uint32_t* out, const uint64_t* out_ptrs, uint32_t B,
-                    hipStream_t s) {
+int launch_mfma8_ct(tfhe_ctx* c, const uint32_t* big, void* dig, const KsOut<uint32_t>& o, uint32_t B, hipStream_t s) {
     const int n = (int)c->p.n, kN = (int)(c->p.k * c->p.N);
     KsPlace pl;
     pl.tiles = c->ks_wp / 16;
@@ -555,58 +589,61 @@ int launch_mfma8_ct(tfhe_ctx* c, const uint32_t* big, void* dig, uint32_t* out, 
     pl.per = (pl.tiles * pl.groups * pl.slices + 7) / 8;
     const double table = 4.0 * c->ks_wp * kN * 32, inputs = 2.0 * B * kN;
     pl.tile_major = table > inputs ? 1 : 0;
+    uint32_t* const sums = ks_sum_rows(o, pl.slices);
     hipLaunchKernelGGL((ks_digits_kernel<uint32_t, uint16_t, true>), dim3(kN / 64, (B + 63) / 64), dim3(THREADS), 0, s,
-                       big, (uint16_t*)dig, (int)B, kN, 16, n, out, out_ptrs, pl.slices > 1);
+                       big, (uint16_t*)dig, (int)B, kN, 16, n, sums);
     auto k = pl.slices > 1 ? ks_mfma8_kernel<KM_CT, true> : ks_mfma8_kernel<KM_CT, false>;
-    hipLaunchKernelGGL(k, dim3(8 * pl.per), dim3(THREADS), 0, s, big, (const uint4*)dig, (const int8_t*)c->d_ksk8, out,
-                       out_ptrs, (int)B, n, kN, c->ks_wp, pl);
+    hipLaunchKernelGGL(k, dim3(8 * pl.per), dim3(THREADS), 0, s, big, (const uint4*)dig, (const int8_t*)c->d_ksk8,
+                       sums ? sums : o.out, sums ? nullptr : o.ptrs, (int)B, n, kN, c->ks_wp, pl);
+    launch_ks_store(o, pl.slices, B, n, s);
     return hip_check(c, hipGetLastError(), "launch ks_mfma8");
 }
 
-int launch_mfma8(tfhe_ctx* c, const uint32_t* big, void* dig, uint32_t* out, const uint64_t* out_ptrs, uint32_t B,
-                 hipStream_t s) {
+int launch_mfma8(tfhe_ctx* c, const uint32_t* big, void* dig, const KsOut<uint32_t>& o, uint32_t B, hipStream_t s) {
     const int cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
     const int64_t wgs4 = (int64_t)(c->ks_wp / 16) * ((B + 255) / 256);
     // 2 ciphertext tiles per wave until 4 fill the CUs twice over (2048
     // ciphertexts: 200 us at 2, 245 us at 4; 4096 326 us at 4, 470 us at 2)
-    if (wgs4 < 2 * cus) return launch_mfma8_ct<2>(c, big, dig, out, out_ptrs, B, s);
-    return launch_mfma8_ct<4>(c, big, dig, out, out_ptrs, B, s);
+    if (wgs4 < 2 * cus) return launch_mfma8_ct<2>(c, big, dig, o, B, s);
+    return launch_mfma8_ct<4>(c, big, dig, o, B, s);
 }
 
 template <int V, typename D, int TW, int KM_CT>
-int launch_mfma_ct(tfhe_ctx* c, const uint32_t* big, D* dig, uint32_t* out, const uint64_t* out_ptrs,
-                   uint32_t B, hipStream_t s) {
+int launch_mfma_ct(tfhe_ctx* c, const uint32_t* big, D* dig, const KsOut<uint32_t>& o, uint32_t B, hipStream_t s) {
     const int n = (int)c->p.n, kN = (int)(c->p.k * c->p.N), t = (int)c->p.ks_t, bb = (int)c->p.ks_base_bits;
     KsPlace pl;
     pl.tiles = (c->ks_wp / 16 + TW - 1) / TW;
     pl.groups = (int)((B + 64 * KM_CT - 1) / (64 * KM_CT));
     pl.slices = ks_slices(c, pl.tiles * pl.groups, kN * t * V / 64, 4);
     pl.per = (pl.tiles * pl.groups * pl.slices + 7) / 8;
+    uint32_t* const sums = ks_sum_rows(o, pl.slices);
     hipLaunchKernelGGL((ks_digits_kernel<uint32_t, D>), dim3((kN + 63) / 64, (B + 63) / 64), dim3(THREADS), 0, s,
-                       big, dig, (int)B, kN, t * bb, n, out, out_ptrs, pl.slices > 1);
+                       big, dig, (int)B, kN, t * bb, n, sums);
     const double table = 4.0 * c->ks_wp * kN * t * V, inputs = (double)B * kN * sizeof(D);
     pl.tile_major = table > inputs ? 1 : 0;
     auto k = pl.slices > 1 ? ks_mfma_kernel<V, D, TW, KM_CT, true> : ks_mfma_kernel<V, D, TW, KM_CT, false>;
     hipLaunchKernelGGL(k, dim3(8 * pl.per), dim3(THREADS), 0, s, big, (const D*)dig,
-                       (const int8_t*)c->d_ksk8, out, out_ptrs, (int)B, n, kN, t, bb, c->ks_wp, pl);
+                       (const int8_t*)c->d_ksk8, sums ? sums : o.out, sums ? nullptr : o.ptrs, (int)B, n, kN, t, bb,
+                       c->ks_wp, pl);
+    launch_ks_store(o, pl.slices, B, n, s);
     return hip_check(c, hipGetLastError(), "launch ks_mfma");
 }
 
 template <int V, typename D, int TW>
-int launch_mfma_ks(tfhe_ctx* c, const uint32_t* big, void* dig_ws, uint32_t* out, const uint64_t* out_ptrs,
-                   uint32_t B, hipStream_t s) {
+int launch_mfma_ks(tfhe_ctx* c, const uint32_t* big, void* dig_ws, const KsOut<uint32_t>& o, uint32_t B,
+                   hipStream_t s) {
     D* dig = (D*)dig_ws;
     // 4 ciphertext tiles per wave, or 2 when that leaves CUs idle (measured:
     // 4096 ciphertexts at n = 64 0.069 -> 0.052 ms; 4 is faster once the grid
     // fills the chip)
     const int cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
     const int64_t wgs4 = (int64_t)((c->ks_wp / 16 + TW - 1) / TW) * ((B + 255) / 256);
-    if (wgs4 < cus) return launch_mfma_ct<V, D, TW, 2>(c, big, dig, out, out_ptrs, B, s);
-    return launch_mfma_ct<V, D, TW, 4>(c, big, dig, out, out_ptrs, B, s);
+    if (wgs4 < cus) return launch_mfma_ct<V, D, TW, 2>(c, big, dig, o, B, s);
+    return launch_mfma_ct<V, D, TW, 4>(c, big, dig, o, B, s);
 }
 
 template <typename T, typename D, int V, int WPW, int P>
-int launch_p(tfhe_ctx* c, const T* big, void* dig_ws, T* out, const uint64_t* out_ptrs, uint32_t B, hipStream_t s) {
+int launch_p(tfhe_ctx* c, const T* big, void* dig_ws, const KsOut<T>& o, uint32_t B, hipStream_t s) {
     const int n = (int)c->p.n, kN = (int)(c->p.k * c->p.N), t = (int)c->p.ks_t, bb = (int)c->p.ks_base_bits;
     constexpr int RS = WPW + Vec16<T>::N;
     const size_t lds = 2ull * P * t * V * RS * sizeof(T);
@@ -619,12 +656,14 @@ int launch_p(tfhe_ctx* c, const T* big, void* dig_ws, T* out, const uint64_t* ou
     auto k = pl.slices > 1 ? keyswitch_kernel<T, D, V, WPW, P, true> : keyswitch_kernel<T, D, V, WPW, P, false>;
     hipError_t e = hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return hip_check(c, e, "hipFuncSetAttribute(keyswitch)");
+    T* const sums = ks_sum_rows(o, pl.slices);
     hipLaunchKernelGGL((ks_digits_kernel<T, D>), dim3((kN + 63) / 64, (B + 63) / 64), dim3(THREADS), 0, s, big, dig,
-                       (int)B, kN, t * bb, n, out, out_ptrs, pl.slices > 1);
+                       (int)B, kN, t * bb, n, sums);
     const double table = (double)kN * t * V * (n + 1), inputs = (double)B * (kN + 1);
     pl.tile_major = table > inputs ? 1 : 0;
-    hipLaunchKernelGGL(k, dim3(8 * pl.per), dim3(THREADS), lds, s, big, (const D*)dig, (const T*)c->d_ksk, out,
-                       out_ptrs, (int)B, n, kN, t, bb, (int)c->ks_row, pl);
+    hipLaunchKernelGGL(k, dim3(8 * pl.per), dim3(THREADS), lds, s, big, (const D*)dig, (const T*)c->d_ksk,
+                       sums ? sums : o.out, sums ? nullptr : o.ptrs, (int)B, n, kN, t, bb, (int)c->ks_row, pl);
+    launch_ks_store(o, pl.slices, B, n, s);
     return hip_check(c, hipGetLastError(), "launch keyswitch");
 }
 
@@ -632,16 +671,16 @@ int launch_p(tfhe_ctx* c, const T* big, void* dig_ws, T* out, const uint64_t* ou
 // whose rows fit the staging registers and that divides kN (fewer barriers
 // for short LWE tiles); with 64-bit words one, which measured faster.
 template <typename T, typename D, int V, int WPW>
-int launch_v(tfhe_ctx* c, const T* big, void* dig, T* out, const uint64_t* out_ptrs, uint32_t B, hipStream_t s) {
+int launch_v(tfhe_ctx* c, const T* big, void* dig, const KsOut<T>& o, uint32_t B, hipStream_t s) {
     const int kN = (int)(c->p.k * c->p.N), t = (int)c->p.ks_t;
     const int E = t * V * WPW;
     if (E > PMAX * THREADS) return ctx_fail(c, TFHE_EINVAL, "key-switching levels exceed the staging tile");
     if constexpr (sizeof(T) == 4) {
-        if (8 * E <= PMAX * THREADS && kN % 8 == 0) return launch_p<T, D, V, WPW, 8>(c, big, dig, out, out_ptrs, B, s);
-        if (4 * E <= PMAX * THREADS && kN % 4 == 0) return launch_p<T, D, V, WPW, 4>(c, big, dig, out, out_ptrs, B, s);
-        if (2 * E <= PMAX * THREADS && kN % 2 == 0) return launch_p<T, D, V, WPW, 2>(c, big, dig, out, out_ptrs, B, s);
+        if (8 * E <= PMAX * THREADS && kN % 8 == 0) return launch_p<T, D, V, WPW, 8>(c, big, dig, o, B, s);
+        if (4 * E <= PMAX * THREADS && kN % 4 == 0) return launch_p<T, D, V, WPW, 4>(c, big, dig, o, B, s);
+        if (2 * E <= PMAX * THREADS && kN % 2 == 0) return launch_p<T, D, V, WPW, 2>(c, big, dig, o, B, s);
     }
-    return launch_p<T, D, V, WPW, 1>(c, big, dig, out, out_ptrs, B, s);
+    return launch_p<T, D, V, WPW, 1>(c, big, dig, o, B, s);
 }
 
 // 16 words per lane.  For short LWE (n + 1 <= 128) 8 words per lane would
@@ -649,31 +688,30 @@ int launch_v(tfhe_ctx* c, const T* big, void* dig, T* out, const uint64_t* out_p
 // input and redo the digit extraction: at n = 64, 16 words measured 30%
 // faster for 32768 ciphertexts and 3% slower for 4096.
 template <typename T, int V>
-int launch_w(tfhe_ctx* c, const void* big, void* dig, void* out, const uint64_t* out_ptrs, uint32_t B,
-             hipStream_t s) {
+int launch_w(tfhe_ctx* c, const void* big, void* dig, const KsOut<T>& o, uint32_t B, hipStream_t s) {
     if constexpr (sizeof(T) == 4) {
         // the MFMA form: a lane's pairs of a chunk must span at most two rows i
         if (c->d_ksk8 && 16 / V <= (int)c->p.ks_t) {
             const uint32_t* b32 = (const uint32_t*)big;
-            uint32_t* o32 = (uint32_t*)out;
-            if (V == 4 && c->p.ks_t == 8) return launch_mfma8(c, b32, dig, o32, out_ptrs, B, s);
-            if (c->p.ks_t * c->p.ks_base_bits <= 16) return launch_mfma_ks<V, uint16_t, 1>(c, b32, dig, o32, out_ptrs, B, s);
-            return launch_mfma_ks<V, uint32_t, 1>(c, b32, dig, o32, out_ptrs, B, s);
+            if (V == 4 && c->p.ks_t == 8) return launch_mfma8(c, b32, dig, o, B, s);
+            if (c->p.ks_t * c->p.ks_base_bits <= 16) return launch_mfma_ks<V, uint16_t, 1>(c, b32, dig, o, B, s);
+            return launch_mfma_ks<V, uint32_t, 1>(c, b32, dig, o, B, s);
         }
     }
     if (c->p.ks_t * c->p.ks_base_bits <= 16)
-        return launch_v<T, uint16_t, V, 16>(c, (const T*)big, dig, (T*)out, out_ptrs, B, s);
-    return launch_v<T, uint32_t, V, 16>(c, (const T*)big, dig, (T*)out, out_ptrs, B, s);
+        return launch_v<T, uint16_t, V, 16>(c, (const T*)big, dig, o, B, s);
+    return launch_v<T, uint32_t, V, 16>(c, (const T*)big, dig, o, B, s);
 }
 
 template <typename T>
-int launch_ks_t(tfhe_ctx* c, const void* big, void* dig, void* out, const uint64_t* out_ptrs, uint32_t B,
+int launch_ks_t(tfhe_ctx* c, const void* big, void* dig, void* out, const uint64_t* out_ptrs, void* sums, uint32_t B,
                 hipStream_t s) {
+    const KsOut<T> o{(T*)out, out_ptrs, (T*)sums};
     switch (c->p.ks_base_bits) {
-        case 1: return launch_w<T, 2>(c, big, dig, out, out_ptrs, B, s);
-        case 2: return launch_w<T, 4>(c, big, dig, out, out_ptrs, B, s);
-        case 3: return launch_w<T, 8>(c, big, dig, out, out_ptrs, B, s);
-        case 4: return launch_w<T, 16>(c, big, dig, out, out_ptrs, B, s);
+        case 1: return launch_w<T, 2>(c, big, dig, o, B, s);
+        case 2: return launch_w<T, 4>(c, big, dig, o, B, s);
+        case 3: return launch_w<T, 8>(c, big, dig, o, B, s);
+        case 4: return launch_w<T, 16>(c, big, dig, o, B, s);
         default: return ctx_fail(c, TFHE_EINVAL, "key-switching base must be 2^1..2^4");
     }
 }
@@ -685,11 +723,12 @@ size_t ks_digits_bytes(const tfhe_ctx* c, uint32_t B) {
     return ((size_t)B * c->p.k * c->p.N * d + 255) & ~(size_t)255;
 }
 
-int launch_keyswitch(tfhe_ctx* c, const void* big_in, void* out, const uint64_t* out_ptrs, uint32_t B, void* dig,
-                     size_t dig_cap, hipStream_t s) {
+int launch_keyswitch(tfhe_ctx* c, const void* big_in, void* out, const uint64_t* out_ptrs, void* sums, uint32_t B,
+                     void* dig, size_t dig_cap, hipStream_t s) {
     if (B == 0) return TFHE_OK;
+    if (out_ptrs && !sums) return ctx_fail(c, TFHE_EINVAL, "key switch to addresses needs rows for its sums");
     if (!dig || dig_cap < ks_digits_bytes(c, B)) return ctx_fail(c, TFHE_EINVAL, "key-switch digit buffer too small");
     TimedLaunch tl(c, s, 1, B);
-    return c->q == 32 ? launch_ks_t<uint32_t>(c, big_in, dig, out, out_ptrs, B, s)
-                      : launch_ks_t<uint64_t>(c, big_in, dig, out, out_ptrs, B, s);
+    return c->q == 32 ? launch_ks_t<uint32_t>(c, big_in, dig, out, out_ptrs, sums, B, s)
+                      : launch_ks_t<uint64_t>(c, big_in, dig, out, out_ptrs, sums, B, s);
 }

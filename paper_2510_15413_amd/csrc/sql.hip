@@ -199,7 +199,7 @@ struct Exec {
                 if ((e = launch_blind_rotate(c, lwe, net.lut_table, net.lut_table ? tvi : nullptr, big, pc.total,
                                              brws, br_b, rs)))
                     break;
-                if ((e = launch_keyswitch(c, big, nullptr, ptrs, pc.total, brws, br_b, rs))) break;
+                if ((e = launch_keyswitch(c, big, nullptr, ptrs, lwe, pc.total, brws, br_b, rs))) break;
             }
             return e;
         };
@@ -609,7 +609,7 @@ extern "C" int sql_server_step(sql_server* sv, void* stream, uint32_t* gates, ui
         if (t.total) {
             if ((rc = launch_combine(c, S.dsegs, S.dstart, (int)nseg, t.total, S.lwe, S.ptrs, S.tvi, s)) ||
                 (rc = launch_blind_rotate(c, S.lwe, nullptr, nullptr, S.big, t.total, S.brws, sv->brws_bytes, s)) ||
-                (rc = launch_keyswitch(c, S.big, nullptr, S.ptrs, t.total, S.brws, sv->brws_bytes, s)))
+                (rc = launch_keyswitch(c, S.big, nullptr, S.ptrs, S.lwe, t.total, S.brws, sv->brws_bytes, s)))
                 return rc;
         }
         if ((rc = hip_check(c, hipEventRecord(S.ev, s), "server tick event"))) return rc;
