@@ -1316,31 +1316,38 @@ int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t
         hipLaunchKernelGGL(l == 2 ? br_fft256_kernel<2> : br_fft256_kernel<0>, dim3(B), dim3(64), 0, s, a);
         return hip_check(c, hipGetLastError(), "launch br_fft256");
     }
+    // The next `count` ciphertexts, per_wg of them per workgroup, in launches of at
+    // most 2^22 workgroups of 512 threads: HIP launches no grid of 2^32 work-items.
+    uint32_t done = 0;
+    const auto part = [&](uint32_t count, uint32_t per_wg, int (*launch)(tfhe_ctx*, const FftArgs&, hipStream_t)) {
+        int rc = TFHE_OK;
+        while (count && !rc) {
+            FftArgs p = a;
+            p.lwe = (const uint8_t*)a.lwe + (size_t)done * (a.n + 1) * word_bytes(c);
+            if (a.tv_index) p.tv_index = a.tv_index + done;
+            p.out = (uint8_t*)a.out + (size_t)done * (c->p.N + 1) * word_bytes(c);
+            p.B = (int)std::min(count, per_wg << 22);
+            done += (uint32_t)p.B;
+            count -= (uint32_t)p.B;
+            rc = launch(c, p, s);
+        }
+        return rc;
+    };
     //                                                       T         R   W  G  L  KD twiddles WPE
     if (c->q == 32) {
-        if (c->p.N == 2048) return l == 3 ? launch_fft_t<Cfg<uint32_t, 16, 8, 1, 3, 2, TW_LDS>>(c, a, s)
-                                          : launch_fft_t<Cfg<uint32_t, 16, 8, 1, 0, 1, TW_LDS>>(c, a, s);
-        uint32_t done = 0;
-        const auto part = [&](uint32_t count, int (*launch)(tfhe_ctx*, const FftArgs&, hipStream_t)) {
-            FftArgs p = a;
-            p.lwe = (const uint32_t*)a.lwe + (size_t)done * (a.n + 1);
-            if (a.tv_index) p.tv_index = a.tv_index + done;
-            p.out = (uint32_t*)a.out + (size_t)done * (c->p.N + 1);
-            p.B = (int)count;
-            done += count;
-            return count ? launch(c, p, s) : TFHE_OK;
-        };
+        if (c->p.N == 2048) return part(B, 1, l == 3 ? launch_fft_t<Cfg<uint32_t, 16, 8, 1, 3, 2, TW_LDS>>
+                                                     : launch_fft_t<Cfg<uint32_t, 16, 8, 1, 0, 1, TW_LDS>>);
         const uint32_t fours = B % (8 * cus) > 6 * cus ? B : B - B % (8 * cus);
-        int rc = part(fours, launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, TW_LDS>>);
+        int rc = part(fours, 4, launch_fft_t<Cfg<uint32_t, 8, 4, 4, 0, 1, TW_LDS>>);
         const uint32_t rest = B - done;
         if (rc || !rest) return rc;
-        if (l != 3) return rest > 2 * cus ? part(rest, launch_fft_t<Cfg<uint32_t, 8, 4, 2, 0, 1, TW_LDS, 3>>)
-                                          : part(rest, launch_fft_t<Cfg<uint32_t, 8, 8, 1, 0, 2, TW_REG>>);
+        if (l != 3) return rest > 2 * cus ? part(rest, 2, launch_fft_t<Cfg<uint32_t, 8, 4, 2, 0, 1, TW_LDS, 3>>)
+                                          : part(rest, 1, launch_fft_t<Cfg<uint32_t, 8, 8, 1, 0, 2, TW_REG>>);
         const uint32_t pairs = rest % (2 * cus) > cus ? rest : rest - rest % (2 * cus);
-        rc = part(pairs, launch_fft_t<Cfg<uint32_t, 8, 8, 2, 3, 4, TW_REG>>);
-        return rc ? rc : part(B - done, launch_fft_t<Cfg<uint32_t, 8, 8, 1, 3, 8, TW_REG>>);
+        rc = part(pairs, 2, launch_fft_t<Cfg<uint32_t, 8, 8, 2, 3, 4, TW_REG>>);
+        return rc ? rc : part(B - done, 1, launch_fft_t<Cfg<uint32_t, 8, 8, 1, 3, 8, TW_REG>>);
     }
-    if (c->p.N == 2048) return l == 4 ? launch_fft_t<Cfg<uint64_t, 16, 8, 1, 4, 2, TW_GLOBAL>>(c, a, s)
-                                      : launch_fft_t<Cfg<uint64_t, 16, 8, 1, 0, 1, TW_GLOBAL>>(c, a, s);
-    return launch_fft_t<Cfg<uint64_t, 8, 8, 1, 0, 4, TW_REG>>(c, a, s);
+    if (c->p.N == 2048) return part(B, 1, l == 4 ? launch_fft_t<Cfg<uint64_t, 16, 8, 1, 4, 2, TW_GLOBAL>>
+                                                 : launch_fft_t<Cfg<uint64_t, 16, 8, 1, 0, 1, TW_GLOBAL>>);
+    return part(B, 1, launch_fft_t<Cfg<uint64_t, 8, 8, 1, 0, 4, TW_REG>>);
 }
