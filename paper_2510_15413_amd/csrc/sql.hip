@@ -221,8 +221,8 @@ struct Exec {
                 put(f, sizeof f);
             }
             put(copies.data(), copies.size() * sizeof(Copy));
-            const uint64_t meta[8] = {(uint64_t)(uintptr_t)net.lut_table, (uint64_t)c->kernel, c->max_batch,
-                                      (uint64_t)c->row_pass, (uint64_t)c->digit_blocks,
+            const uint64_t meta[9] = {(uint64_t)(uintptr_t)net.lut_table, (uint64_t)c->kernel, c->max_batch,
+                                      (uint64_t)c->row_pass, (uint64_t)c->digit_blocks, (uint64_t)c->split_groups,
                                       (uint64_t)(uintptr_t)c->ws, (uint64_t)c->ws_bytes, (uint64_t)br_b};
             put(meta, sizeof meta);
             hipGraphExec_t exec = nullptr;
