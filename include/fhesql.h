@@ -151,8 +151,9 @@ int tfhe_set_kernel(tfhe_ctx* ctx, int kind);
  *                        at a time with component 0 in LDS and the key
  *                        staged in LDS, when it fits.
  *                        Every grouping gives the same output bits.
- * The blind-rotation workspace depends on the row pass and digit grouping
- * (several passes with per-group digits add a digit cache).  Direct calls and
+ * The blind-rotation workspace of the int8 kernels depends on the row pass and
+ * digit grouping (several passes with per-group digits add a digit cache); the
+ * transforms need none.  Direct calls and
  * the level executor size it per call; a server sizes it at creation, and a
  * later tuning that needs more makes sql_server_step return TFHE_EINVAL
  * without launching (restore the tuning, or create a new server). */
@@ -185,8 +186,9 @@ int tfhe_bootstrap_batch(tfhe_ctx* ctx, const void* d_lwe_in, const void* d_test
  * hipMalloc): same arguments and output bits, but the blind-rotation
  * workspace is a static device array of tfhe_noalloc_scratch_bytes() bytes
  * (32 MiB; one copy per device, held until the process ends) and the call
- * allocates nothing and records no timing events.  A batch whose workspace
- * would exceed the array fails with TFHE_ESHAPE before any launch (at the
+ * allocates nothing and records no timing events.  A batch whose workspace on
+ * the int8 kernels would exceed the array fails with TFHE_ESHAPE before any
+ * launch, also where the transforms, which need none, would run it (at the
  * standard 32-bit set up to 4096 ciphertexts fit; parameter sets whose
  * accumulators stay in LDS need none).  The context's device must be
  * current.  Every call on a device shares that device's array: calls that

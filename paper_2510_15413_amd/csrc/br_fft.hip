@@ -1269,16 +1269,27 @@ static bool small_pays(const tfhe_ctx* c, uint32_t B) {
     return full == 0 ? rem <= step * 3 / 4 : full <= 4 && rem <= step / 2 && rem > 0;
 }
 
-// Whether a batch of B takes the transform path: unless a tuning knob asks for
-// a shape of the int8 kernels -- a row pass that is not the ring's default, a
-// digit grouping, or a positive split threshold that covers the batch.  (The
-// default row pass and "never split", which earlier tunings saved, do not.)
-bool fft_usable(const tfhe_ctx* c, uint32_t B) {
-    if (!c->d_fkey || c->digit_blocks != 0) return false;
-    if (c->p.N == 256 && !small_pays(c, B)) return false;
+// Whether the context's batches take the transform path at all: with key spectra
+// and no tuning knob that asks for a shape of the int8 kernels -- a row pass that
+// is not the ring's default or a digit grouping.  (The default row pass and
+// "never split", which earlier tunings saved, do not.)
+static bool fft_selected(const tfhe_ctx* c) {
     const int default_rp = c->p.N == 2048 ? 8 : c->q == 64 || c->p.N == 256 ? 4 : 16;
-    if (c->row_pass != 0 && c->row_pass != default_rp) return false;
+    return c->d_fkey && c->digit_blocks == 0 && (c->row_pass == 0 || c->row_pass == default_rp);
+}
+
+// Whether a batch of B takes it: if no positive split threshold covers the batch
+// and, at N = 256, where it is faster.
+bool fft_usable(const tfhe_ctx* c, uint32_t B) {
+    if (!fft_selected(c) || (c->p.N == 256 && !small_pays(c, B))) return false;
     return !(c->split_groups > 0 && ((uint64_t)B + 15) / 16 <= (uint64_t)c->split_groups);
+}
+
+// A bound on the batches of at most Bmax that do not take it (0: all do).
+uint32_t fft_leaves_upto(const tfhe_ctx* c, uint32_t Bmax) {
+    const uint32_t cus = c->prop.multiProcessorCount > 0 ? c->prop.multiProcessorCount : 256;
+    if (!fft_selected(c) || (c->p.N == 256 && !(Bmax <= 16 * cus && small_pays(c, Bmax)))) return Bmax;
+    return c->split_groups > 0 ? (uint32_t)std::min<uint64_t>(Bmax, 16 * (uint64_t)c->split_groups) : 0;
 }
 
 int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index, void* big_out, uint32_t B,

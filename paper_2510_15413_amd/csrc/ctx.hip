@@ -12,6 +12,7 @@ int launch_br_mfma(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_
 int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index, void* big_out, uint32_t B,
                   hipStream_t s);
 bool fft_usable(const tfhe_ctx* c, uint32_t B);
+uint32_t fft_leaves_upto(const tfhe_ctx* c, uint32_t Bmax);
 int fft_setup(tfhe_ctx* c, hipStream_t s);
 int launch_br_plain(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index,
                     void* big_out, uint32_t B, hipStream_t s);
@@ -440,12 +441,14 @@ extern "C" int tfhe_timing_read(tfhe_ctx* c, int kind, uint64_t* launches, doubl
     return TFHE_OK;
 }
 
+// (the transform kernels and the plain one take no workspace)
 size_t blind_rotate_ws_bytes(const tfhe_ctx* c, uint32_t B) {
-    return c->kernel == TFHE_KERNEL_MFMA ? mfma_ws_bytes(c, B) : 0;
+    return c->kernel == TFHE_KERNEL_MFMA && !fft_usable(c, B) ? mfma_ws_bytes(c, B) : 0;
 }
 
 size_t blind_rotate_ws_bytes_upto(const tfhe_ctx* c, uint32_t Bmax) {
-    return c->kernel == TFHE_KERNEL_MFMA ? mfma_ws_bytes_upto(c, Bmax) : 0;
+    const uint32_t b = c->kernel == TFHE_KERNEL_MFMA ? fft_leaves_upto(c, Bmax) : 0;
+    return b ? mfma_ws_bytes_upto(c, b) : 0;
 }
 
 int launch_blind_rotate(tfhe_ctx* c, const void* lwe_in, const void* testv_table, const int32_t* tv_index,
@@ -464,9 +467,11 @@ extern "C" int tfhe_bootstrap_batch(tfhe_ctx* c, const void* d_lwe_in, const voi
     if (B == 0) return TFHE_OK;
     if (!d_lwe_in || !d_out) return ctx_fail(c, TFHE_EINVAL, "null ciphertext pointer");
     hipStream_t s = (hipStream_t)stream;
-    const size_t need = blind_rotate_ws_bytes(c, B);
-    if (!need) return launch_blind_rotate(c, d_lwe_in, d_testv, nullptr, d_out, B, nullptr, 0, s);
-    int rc = ws_acquire(c, s, need);
+    // A batch that the int8 kernels would run in the workspace keeps its order
+    // with the calls on other streams where the transforms run it without.
+    if (c->kernel != TFHE_KERNEL_MFMA || !mfma_ws_bytes(c, B))
+        return launch_blind_rotate(c, d_lwe_in, d_testv, nullptr, d_out, B, nullptr, 0, s);
+    int rc = ws_acquire(c, s, blind_rotate_ws_bytes(c, B));
     if (rc) return rc;
     rc = launch_blind_rotate(c, d_lwe_in, d_testv, nullptr, d_out, B, c->ws, c->ws_bytes, s);
     const int rr = ws_release(c, s);

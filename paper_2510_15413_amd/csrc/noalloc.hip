@@ -12,6 +12,7 @@ int launch_br_mfma(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_
 int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index, void* big_out, uint32_t B,
                   hipStream_t s);
 bool fft_usable(const tfhe_ctx* c, uint32_t B);
+size_t mfma_ws_bytes(const tfhe_ctx* c, uint32_t B);
 int launch_br_plain(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index,
                     void* big_out, uint32_t B, hipStream_t s);
 
@@ -59,7 +60,9 @@ extern "C" int tfhe_bootstrap_batch_noalloc(tfhe_ctx* c, const void* d_lwe_in, c
     if (rc) return rc;
     if (dev != c->device || dev < 0 || dev >= kMaxDevices)
         return ctx_fail(c, TFHE_EINVAL, "the context's device must be the current device");
-    const size_t need = blind_rotate_ws_bytes(c, B);
+    // (the int8 kernels' need, whichever kernel runs: the batches that are taken
+    // do not depend on the knobs that choose between them)
+    const size_t need = c->kernel == TFHE_KERNEL_MFMA ? mfma_ws_bytes(c, B) : 0;
     if (need > kScratchBytes) {
         char msg[160];
         snprintf(msg, sizeof msg, "a batch of %u needs %zu bytes of scratch, more than the %zu-byte static array", B,

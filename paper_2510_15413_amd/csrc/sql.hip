@@ -24,6 +24,8 @@
 
 #include "fhesql_internal.h"
 
+size_t mfma_ws_bytes_upto(const tfhe_ctx* c, uint32_t Bmax);
+
 // ------------------------------------------------------------- combine
 
 namespace {
@@ -437,8 +439,10 @@ extern "C" int sql_server_create(tfhe_ctx* c, size_t budget, uint32_t max_batch,
                         (c->q == 32 && c->p.N == 1024 ? c->fkey_bytes : 0) + c->ksk8_bytes;
     const size_t lwe_b = al256((size_t)max_batch * lw * wb), big_b = al256((size_t)max_batch * bw * wb);
     const size_t ptr_b = al256((size_t)max_batch * 8), tvi_b = al256((size_t)max_batch * 4);
-    // blind-rotation workspace, reused by the key switch's digits
-    const size_t br_b = std::max(al256(blind_rotate_ws_bytes_upto(c, max_batch)), al256(ks_digits_bytes(c, max_batch)));
+    // blind-rotation workspace (the int8 kernels', which a later tuning may ask
+    // for), reused by the key switch's digits
+    const size_t br_b = std::max(al256(c->kernel == TFHE_KERNEL_MFMA ? mfma_ws_bytes_upto(c, max_batch) : 0),
+                                 al256(ks_digits_bytes(c, max_batch)));
     const size_t seg_b = al256(cap * sizeof(Segment)), st_b = al256(cap * 4);
     const size_t set_b = lwe_b + big_b + ptr_b + tvi_b + br_b + seg_b + st_b;
     sv->book.fixed = keys + 2 * set_b;
