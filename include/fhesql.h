@@ -153,10 +153,13 @@ int tfhe_set_kernel(tfhe_ctx* ctx, int kind);
  *                        Every grouping gives the same output bits.
  * The blind-rotation workspace of the int8 kernels depends on the row pass and
  * digit grouping (several passes with per-group digits add a digit cache); the
- * transforms need none.  Direct calls and
- * the level executor size it per call; a server sizes it at creation, and a
- * later tuning that needs more makes sql_server_step return TFHE_EINVAL
- * without launching (restore the tuning, or create a new server). */
+ * transforms need none.  Direct calls and the level executor size it per call;
+ * a server sizes it at creation.  A later tuning that sends its ticks from the
+ * transforms to the int8 kernels makes it take, within its budget, the
+ * workspace those needed under the tuning at creation; one that needs more than
+ * that, or than the budget has room for, makes sql_server_step return
+ * TFHE_EINVAL without launching (restore the tuning and step again, or create a
+ * new server). */
 #define TFHE_TUNE_DIGIT_BLOCKS 3
 /*   TFHE_TUNE_SPLIT_GROUPS for N >= 256, a blind rotation of at most this
  *                        many groups of 16 ciphertexts runs each step as two
@@ -372,9 +375,9 @@ typedef struct sql_sum_query {
     void* d_sum;            /* [w + ceil(log2 rows)][n+1] result */
 } sql_sum_query;
 
-/* hbm_budget_bytes: total device memory the server may account for (keys --
- * the transforms of the BSK only with torus_bits = 32 and N = 1024 --,
- * two staging sets, temporaries); max_batch: gates per tick. */
+/* hbm_budget_bytes: total device memory the server may account for (keys and
+ * what the context derives from them, two staging sets, temporaries);
+ * max_batch: gates per tick. */
 int sql_server_create(tfhe_ctx* ctx, size_t hbm_budget_bytes, uint32_t max_batch,
                       sql_server** out);
 void sql_server_destroy(sql_server* srv);

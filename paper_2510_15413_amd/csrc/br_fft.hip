@@ -1211,12 +1211,13 @@ std::vector<d2> small_table() {
 // twiddles behind them, and uploads those; no room leaves d_fkey null.
 int setup_tables(tfhe_ctx* c, size_t per_poly, const std::vector<d2>& tw) {
     const size_t key_bytes = (size_t)c->p.n * 2 * c->p.l * 2 * per_poly * sizeof(d2);
-    if (hipMalloc(&c->d_fkey, key_bytes + tw.size() * sizeof(d2)) != hipSuccess) {
+    const size_t bytes = key_bytes + tw.size() * sizeof(d2);
+    if (hipMalloc(&c->d_fkey, bytes) != hipSuccess) {
         (void)hipGetLastError();
         c->d_fkey = nullptr;
         return TFHE_OK;
     }
-    c->fkey_bytes = key_bytes;
+    c->fkey_bytes = bytes;
     c->d_ftw = (uint8_t*)c->d_fkey + key_bytes;
     return hip_check(c, hipMemcpy(c->d_ftw, tw.data(), tw.size() * sizeof(d2), hipMemcpyHostToDevice),
                      "copy twiddles");

@@ -100,7 +100,7 @@ struct tfhe_ctx {
     void* d_bsk = nullptr;     // [n][(k+1)l][k+1][N] words
     int8_t* d_bsk8 = nullptr;  // [n][(k+1)l][k+1][LIMBS][2N] Toeplitz limb form
     void* d_fkey = nullptr;    // [n][(k+1)l][k+1][limbs][N/2] key spectra (N = 256 at q = 32, 1024, 2048), or null
-    size_t fkey_bytes = 0;
+    size_t fkey_bytes = 0;     // with the twiddles behind them
     void* d_ftw = nullptr;     // twiddles of the transform path (in d_fkey's allocation)
     void* d_ksk = nullptr;     // [kN][t][2^b][ks_row] words (rows padded to whole 128-byte lines)
     size_t ks_row = 0;         // words per KSK row on the device: n+1 rounded up to 128 bytes

@@ -835,6 +835,31 @@ struct ServerBook {
         ticks++;
     }
 
+    // How far every active query has been issued, and going back there (a tick
+    // that could not be launched).
+    struct Mark {
+        size_t level, seg;
+        uint32_t row;
+        bool copies_done;
+        uint64_t last_tick;
+    };
+    std::vector<Mark> mark() const {
+        std::vector<Mark> m;
+        for (const ServerQuery* q : active) m.push_back(Mark{q->level, q->seg, q->row, q->copies_done, q->last_tick});
+        return m;
+    }
+    void rewind(const std::vector<Mark>& m) {
+        for (size_t i = 0; i < m.size(); i++) {
+            ServerQuery* q = active[i];
+            q->level = m[i].level;
+            q->seg = m[i].seg;
+            q->row = m[i].row;
+            q->copies_done = m[i].copies_done;
+            q->last_tick = m[i].last_tick;
+        }
+        ticks--;
+    }
+
     // Retires the queries whose last level ran in a tick before `completed`
     // (every tick numbered below it has finished on the device);
     // release(base) frees a query's temporaries.

@@ -397,6 +397,7 @@ extern "C" int sql_expr_eval(tfhe_ctx* c, const void* const* d_cols, uint32_t nc
 // ServerBook's.
 struct ServerStage {
     uint8_t *lwe = nullptr, *big = nullptr, *brws = nullptr;
+    uint8_t* brws0 = nullptr;  // the workspace in the server's staging memory
     uint64_t* ptrs = nullptr;
     int32_t* tvi = nullptr;
     Segment* dsegs = nullptr;
@@ -412,7 +413,10 @@ struct sql_server {
     tfhe_ctx* c = nullptr;
     ServerBook book;
     void* stage = nullptr;
-    size_t brws_bytes = 0;
+    size_t brws_bytes = 0;             // workspace of a set: the one in `stage`, or the one in `late`
+    size_t brws0_bytes = 0;            // the one in `stage`
+    size_t late_bytes = 0;             // workspace of a set for the int8 kernels under the tuning at creation
+    void* late = nullptr;              // both sets' (taken with the first tick that needs it), or null
     ServerStage st[2];
     uint64_t completed = 0;            // every tick numbered below has finished
     hipStream_t last_stream = nullptr; // stream of the last tick enqueued
@@ -431,18 +435,15 @@ extern "C" int sql_server_create(tfhe_ctx* c, size_t budget, uint32_t max_batch,
     const size_t cap = sv->book.seg_cap;
     const size_t wb = word_bytes(c), lw = c->p.n + 1, bw = (size_t)c->p.k * c->p.N + 1;
     const size_t NL = c->q == 32 ? 4 : 8;
-    // (the key spectra are counted at q = 32, N = 1024 only: at the other rings
-    // they can exceed all the other keys, and a budget that held a server
-    // before a context kept them still does)
     const size_t keys = (tfhe_bsk_words(&c->p) + tfhe_ksk_words(&c->p)) * wb +
-                        (size_t)c->p.n * 2 * c->p.l * 2 * NL * 2 * c->p.N +
-                        (c->q == 32 && c->p.N == 1024 ? c->fkey_bytes : 0) + c->ksk8_bytes;
+                        (size_t)c->p.n * 2 * c->p.l * 2 * NL * 2 * c->p.N + c->fkey_bytes + c->ksk8_bytes;
     const size_t lwe_b = al256((size_t)max_batch * lw * wb), big_b = al256((size_t)max_batch * bw * wb);
     const size_t ptr_b = al256((size_t)max_batch * 8), tvi_b = al256((size_t)max_batch * 4);
-    // blind-rotation workspace (the int8 kernels', which a later tuning may ask
-    // for), reused by the key switch's digits
-    const size_t br_b = std::max(al256(c->kernel == TFHE_KERNEL_MFMA ? mfma_ws_bytes_upto(c, max_batch) : 0),
-                                 al256(ks_digits_bytes(c, max_batch)));
+    // blind-rotation workspace of the kernels that run, reused by the key
+    // switch's digits; the int8 kernels' is taken if a later tuning asks for them
+    const size_t dig_b = al256(ks_digits_bytes(c, max_batch));
+    const size_t br_b = std::max(al256(blind_rotate_ws_bytes_upto(c, max_batch)), dig_b);
+    sv->late_bytes = c->kernel == TFHE_KERNEL_MFMA ? std::max(al256(mfma_ws_bytes_upto(c, max_batch)), dig_b) : 0;
     const size_t seg_b = al256(cap * sizeof(Segment)), st_b = al256(cap * 4);
     const size_t set_b = lwe_b + big_b + ptr_b + tvi_b + br_b + seg_b + st_b;
     sv->book.fixed = keys + 2 * set_b;
@@ -462,7 +463,7 @@ extern "C" int sql_server_create(tfhe_ctx* c, size_t budget, uint32_t max_batch,
         S.big = p; p += big_b;
         S.ptrs = (uint64_t*)p; p += ptr_b;
         S.tvi = (int32_t*)p; p += tvi_b;
-        S.brws = p; p += br_b;
+        S.brws = S.brws0 = p; p += br_b;
         S.dsegs = (Segment*)p; p += seg_b;
         S.dstart = (uint32_t*)p;
     }
@@ -470,7 +471,7 @@ extern "C" int sql_server_create(tfhe_ctx* c, size_t budget, uint32_t max_batch,
         sql_server_destroy(sv);
         return rc;
     }
-    sv->brws_bytes = br_b;
+    sv->brws_bytes = sv->brws0_bytes = br_b;
     sv->book.in_use = sv->book.fixed;
     *out = sv;
     return TFHE_OK;
@@ -482,6 +483,7 @@ extern "C" void sql_server_destroy(sql_server* sv) {
     sv->book.clear([](uint64_t base) { if (base) hipFreeAsync((void*)(uintptr_t)base, nullptr); });
     hipDeviceSynchronize();
     if (sv->stage) hipFree(sv->stage);
+    if (sv->late) hipFree(sv->late);
     for (auto& S : sv->st) {
         if (S.hsegs) hipHostFree(S.hsegs);
         if (S.hstart) hipHostFree(S.hstart);
@@ -554,6 +556,26 @@ static int server_poll(sql_server* sv, int k, bool wait) {
     return TFHE_OK;
 }
 
+// The workspace of a tick of B gates: the one the server was created with, or,
+// where a later tuning sends the tick to the int8 kernels, their own, which the
+// server then takes and accounts for.
+static int server_workspace(sql_server* sv, uint32_t B) {
+    tfhe_ctx* c = sv->c;
+    const size_t need = blind_rotate_ws_bytes(c, B);
+    if (need <= sv->brws_bytes) return TFHE_OK;
+    if (sv->late || need > sv->late_bytes || sv->book.in_use + 2 * sv->late_bytes > sv->book.budget)
+        return ctx_fail(c, TFHE_EINVAL, "blind-rotation workspace too small for the current tuning");
+    int rc = hip_check(c, hipMalloc(&sv->late, 2 * sv->late_bytes), "server int8 workspace");
+    if (rc) {
+        sv->late = nullptr;
+        return rc;
+    }
+    for (int k = 0; k < 2; k++) sv->st[k].brws = (uint8_t*)sv->late + k * sv->late_bytes;
+    sv->book.in_use += 2 * sv->late_bytes;
+    sv->brws_bytes = sv->late_bytes;
+    return TFHE_OK;
+}
+
 extern "C" int sql_server_step(sql_server* sv, void* stream, uint32_t* gates, uint32_t* active, uint32_t* queued) {
     if (!sv) return TFHE_EINVAL;
     tfhe_ctx* c = sv->c;
@@ -568,17 +590,30 @@ extern "C" int sql_server_step(sql_server* sv, void* stream, uint32_t* gates, ui
     // temporaries go back to the stream-ordered pool after the ticks that used them
     bk.retire([&](uint64_t base) { hipFreeAsync((void*)(uintptr_t)base, s); }, sv->completed);
     std::string why;
-    rc = bk.admit(
-        [&](size_t bytes) -> uint64_t {
-            void* p = nullptr;
-            return hipMallocAsync(&p, bytes, s) == hipSuccess ? (uint64_t)(uintptr_t)p : 0;
-        },
-        &why);
-    if (rc) return ctx_fail(c, rc, why);
+    const auto alloc = [&](size_t bytes) -> uint64_t {
+        void* p = nullptr;
+        return hipMallocAsync(&p, bytes, s) == hipSuccess ? (uint64_t)(uintptr_t)p : 0;
+    };
+    if ((rc = bk.admit(alloc, &why))) return ctx_fail(c, rc, why);
+    if (sv->late && bk.active.empty() && !bk.queue.empty()) {
+        // nothing runs and the next query does not fit beside the int8 workspace
+        if ((rc = server_poll(sv, 0, true)) || (rc = server_poll(sv, 1, true))) return rc;
+        hipFree(sv->late);
+        sv->late = nullptr;
+        for (auto& S : sv->st) S.brws = S.brws0;
+        sv->brws_bytes = sv->brws0_bytes;
+        bk.in_use -= 2 * sv->late_bytes;
+        if ((rc = bk.admit(alloc, &why))) return ctx_fail(c, rc, why);
+    }
     const size_t wb = word_bytes(c);
     Tick t;
     const uint64_t tick_no = bk.ticks;
+    const auto mark = bk.mark();
     bk.next_tick(t, wb);
+    if (t.total && (rc = server_workspace(sv, t.total))) {
+        bk.rewind(mark);  // the tick is issued again when there is room, or the tuning is restored
+        return rc;
+    }
     const size_t nseg = t.segs.size();
     const bool work = t.total || !t.lins.empty() || !t.copies.empty();
     if (work) {
