@@ -4,14 +4,14 @@ It times candidate settings of the library's tuning knobs on the caller's
 own workload and keeps the fastest: ciphertexts per blind-rotation launch
 (how a level's gates are cut into launches), MFMA row tiles per pass (the
 Toeplitz tile height a workgroup covers per pass; at 1024 and 2048
-coefficients the default one stands for the transform kernels) and, for rings
-of 512 coefficients or more, the batch size below which a blind rotation
-spreads each 16-ciphertext group over many workgroups.  No knob changes an output
-bit, so the choice only affects time.  The tile width -- ciphertexts per
-tile -- is the MFMA operand's 16 columns and is not a knob (32 ciphertexts
-per workgroup, two tiles sharing each key fragment, measured no faster at
-the toy size).  Results are cached per (GPU, parameter values, workload key)
-in a JSON file so a serving process tunes once.
+coefficients the default one stands for the transform kernels, any other for
+the int8 ones) and, for rings of 512 coefficients or more, the batch size below
+which a blind rotation spreads each 16-ciphertext group over many workgroups.
+No knob changes an output bit, so the choice only affects time.  The tile width
+-- ciphertexts per tile -- is the MFMA operand's 16 columns and is not a knob
+(32 ciphertexts per workgroup, two tiles sharing each key fragment, measured no
+faster at the toy size).  Results are cached per (GPU, parameter values, kernels
+of the ring, workload key) in a JSON file so a serving process tunes once.
 """
 from __future__ import annotations
 
@@ -37,8 +37,13 @@ def _gpu_name():
 
 
 def cache_key(p, key):
-    """Cache entry name: the GPU, the parameter values and the workload key."""
-    return f"{_gpu_name()}|q{p.q} n{p.n} N{p.N} l{p.l} bg{p.bg_bits} ks{p.ks_bits}x{p.ks_t}|{key}"
+    """Cache entry name: the GPU, the parameter values, the kernels that the ring
+    runs by default and the workload key.  (Entries without "transforms" at a
+    ring that has them were saved when it had none: they chose between the int8
+    kernels' row passes, and one of those would keep the context on the int8
+    kernels, which take 2.5 to 8 times as long.)"""
+    transforms = " transforms" if p.N in (1024, 2048) or (p.q, p.N) == (32, 256) else ""
+    return f"{_gpu_name()}|q{p.q} n{p.n} N{p.N} l{p.l} bg{p.bg_bits} ks{p.ks_bits}x{p.ks_t}{transforms}|{key}"
 
 
 def tune(ctx, key, run, cands=None, reps=1, cache_path=DEFAULT_CACHE, log=None):
