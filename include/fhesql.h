@@ -174,6 +174,13 @@ int tfhe_set_tuning(tfhe_ctx* ctx, int key, int64_t value);
 /* Current value of a tuning knob (as set, 0 or -1 for the defaults). */
 int tfhe_get_tuning(tfhe_ctx* ctx, int key, int64_t* value);
 
+/* The kernels that a blind rotation of B ciphertexts runs on under the current
+ * kernel selection and tuning (host only; TFHE_EINVAL for a null context). */
+#define TFHE_ROUTE_PLAIN 0     /* scalar integers */
+#define TFHE_ROUTE_INT8 1      /* int8 MFMA products */
+#define TFHE_ROUTE_TRANSFORM 2 /* double-precision transforms */
+int tfhe_blind_rotation_route(const tfhe_ctx* ctx, uint32_t B);
+
 /* Waits for the stream and reports any asynchronous fault. */
 int tfhe_ctx_sync(tfhe_ctx* ctx, void* hip_stream);
 

@@ -36,6 +36,7 @@ EXPORTS = [
     "sql_server_step", "sql_server_done", "sql_server_bytes_in_use",
     "sql_radix_mask_scan", "sql_radix_masked_select", "sql_radix_sum", "sql_expr_eval", "tfhe_timing_log", "sql_server_submit_expr",
     "tfhe_graph_stats", "tfhe_bootstrap_batch_noalloc", "tfhe_noalloc_scratch_bytes", "tfhe_get_tuning",
+    "tfhe_blind_rotation_route",
 ]
 # Expression-tree node kinds and comparison operators (sql_expr).
 SQL_EXPR_KINDS = {"column": 0, "const": 1, "literal": 2, "cmp": 3, "and": 4, "or": 5, "xor": 6, "not": 7,
@@ -128,6 +129,7 @@ def load():
         "tfhe_bootstrap_batch_noalloc": (i32, [vp, vp, vp, vp, u32, vp]),
         "tfhe_noalloc_scratch_bytes": (sz, []),
         "tfhe_get_tuning": (i32, [vp, i32, ctypes.POINTER(ctypes.c_int64)]),
+        "tfhe_blind_rotation_route": (i32, [vp, u32]),
     }
     for name, (res, args) in sig.items():
         f = getattr(L, name)
@@ -261,6 +263,10 @@ class Context:
             self._rc(L.tfhe_set_tuning(self._h, TFHE_TUNE_MAX_BATCH, int(max_batch)), "tfhe_set_tuning")
         if row_pass is not None:
             self._rc(L.tfhe_set_tuning(self._h, TFHE_TUNE_ROW_PASS, int(row_pass)), "tfhe_set_tuning")
+
+    def blind_rotation_route(self, B):
+        """Kernels of a blind rotation of B ciphertexts: 'plain', 'int8' or 'transform'."""
+        return ("plain", "int8", "transform")[load().tfhe_blind_rotation_route(self._h, B)]
 
     # -- evaluation -------------------------------------------------------
     def set_kernel(self, kind):

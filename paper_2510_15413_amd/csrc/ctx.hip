@@ -441,9 +441,18 @@ extern "C" int tfhe_timing_read(tfhe_ctx* c, int kind, uint64_t* launches, doubl
     return TFHE_OK;
 }
 
-// (the transform kernels and the plain one take no workspace)
+// The kernels of a batch of B: what every launch, and every size, goes by.
+int blind_rotate_route(const tfhe_ctx* c, uint32_t B) {
+    if (c->kernel == TFHE_KERNEL_PLAIN) return TFHE_ROUTE_PLAIN;
+    return fft_usable(c, B) ? TFHE_ROUTE_TRANSFORM : TFHE_ROUTE_INT8;
+}
+
+extern "C" int tfhe_blind_rotation_route(const tfhe_ctx* c, uint32_t B) {
+    return c ? blind_rotate_route(c, B) : TFHE_EINVAL;
+}
+
 size_t blind_rotate_ws_bytes(const tfhe_ctx* c, uint32_t B) {
-    return c->kernel == TFHE_KERNEL_MFMA && !fft_usable(c, B) ? mfma_ws_bytes(c, B) : 0;
+    return blind_rotate_route(c, B) == TFHE_ROUTE_INT8 ? mfma_ws_bytes(c, B) : 0;
 }
 
 size_t blind_rotate_ws_bytes_upto(const tfhe_ctx* c, uint32_t Bmax) {
@@ -456,9 +465,11 @@ int launch_blind_rotate(tfhe_ctx* c, const void* lwe_in, const void* testv_table
     if (B == 0) return TFHE_OK;
     const void* tv = testv_table ? testv_table : c->d_gate_tv;
     TimedLaunch tl(c, s, 0, B);
-    if (c->kernel == TFHE_KERNEL_PLAIN) return launch_br_plain(c, lwe_in, tv, tv_index, big_out, B, s);
-    if (fft_usable(c, B)) return launch_br_fft(c, lwe_in, tv, tv_index, big_out, B, s);
-    return launch_br_mfma(c, lwe_in, tv, tv_index, big_out, B, ws, ws_cap, s);
+    switch (blind_rotate_route(c, B)) {
+        case TFHE_ROUTE_PLAIN: return launch_br_plain(c, lwe_in, tv, tv_index, big_out, B, s);
+        case TFHE_ROUTE_TRANSFORM: return launch_br_fft(c, lwe_in, tv, tv_index, big_out, B, s);
+        default: return launch_br_mfma(c, lwe_in, tv, tv_index, big_out, B, ws, ws_cap, s);
+    }
 }
 
 extern "C" int tfhe_bootstrap_batch(tfhe_ctx* c, const void* d_lwe_in, const void* d_testv, void* d_out,

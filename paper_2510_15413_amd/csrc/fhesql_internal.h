@@ -187,6 +187,7 @@ int launch_bsk_limbs(tfhe_ctx* c, hipStream_t s);
 int launch_blind_rotate(tfhe_ctx* c, const void* lwe_in, const void* testv_table,
                         const int32_t* tv_index, void* big_out, uint32_t B, void* ws,
                         size_t ws_cap, hipStream_t s);
+int blind_rotate_route(const tfhe_ctx* c, uint32_t B);  // TFHE_ROUTE_*
 size_t blind_rotate_ws_bytes(const tfhe_ctx* c, uint32_t B);
 // Largest blind-rotation workspace of any batch of at most Bmax ciphertexts.
 size_t blind_rotate_ws_bytes_upto(const tfhe_ctx* c, uint32_t Bmax);

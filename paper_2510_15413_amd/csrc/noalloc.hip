@@ -11,7 +11,6 @@ int launch_br_mfma(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_
                    void* big_out, uint32_t B, void* ws, size_t ws_cap, hipStream_t s);
 int launch_br_fft(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index, void* big_out, uint32_t B,
                   hipStream_t s);
-bool fft_usable(const tfhe_ctx* c, uint32_t B);
 size_t mfma_ws_bytes(const tfhe_ctx* c, uint32_t B);
 int launch_br_plain(tfhe_ctx* c, const void* lwe_in, const void* tv, const int32_t* tv_index,
                     void* big_out, uint32_t B, hipStream_t s);
@@ -74,7 +73,9 @@ extern "C" int tfhe_bootstrap_batch_noalloc(tfhe_ctx* c, const void* d_lwe_in, c
     // no timing events: creating them could allocate
     const void* tv = d_testv ? d_testv : c->d_gate_tv;
     hipStream_t s = (hipStream_t)stream;
-    if (c->kernel == TFHE_KERNEL_PLAIN) return launch_br_plain(c, d_lwe_in, tv, nullptr, d_out, B, s);
-    if (fft_usable(c, B)) return launch_br_fft(c, d_lwe_in, tv, nullptr, d_out, B, s);
-    return launch_br_mfma(c, d_lwe_in, tv, nullptr, d_out, B, ptr, kScratchBytes, s);
+    switch (blind_rotate_route(c, B)) {
+        case TFHE_ROUTE_PLAIN: return launch_br_plain(c, d_lwe_in, tv, nullptr, d_out, B, s);
+        case TFHE_ROUTE_TRANSFORM: return launch_br_fft(c, d_lwe_in, tv, nullptr, d_out, B, s);
+        default: return launch_br_mfma(c, d_lwe_in, tv, nullptr, d_out, B, ptr, kScratchBytes, s);
+    }
 }
