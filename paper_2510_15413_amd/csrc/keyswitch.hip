@@ -585,14 +585,16 @@ int launch_mfma8_ct(tfhe_ctx* c, const uint32_t* big, void* dig, const KsOut<uin
     KsPlace pl;
     pl.tiles = c->ks_wp / 16;
     pl.groups = (int)((B + 64 * KM_CT - 1) / (64 * KM_CT));
-    pl.slices = ks_slices(c, pl.tiles * pl.groups, kN / 8, 4, 2);
+    // (4 tiles per wave are taken where they fill the CUs twice over: one slice)
+    pl.slices = KM_CT == 2 ? ks_slices(c, pl.tiles * pl.groups, kN / 8, 4, 2) : 1;
     pl.per = (pl.tiles * pl.groups * pl.slices + 7) / 8;
     const double table = 4.0 * c->ks_wp * kN * 32, inputs = 2.0 * B * kN;
     pl.tile_major = table > inputs ? 1 : 0;
     uint32_t* const sums = ks_sum_rows(o, pl.slices);
     hipLaunchKernelGGL((ks_digits_kernel<uint32_t, uint16_t, true>), dim3(kN / 64, (B + 63) / 64), dim3(THREADS), 0, s,
                        big, (uint16_t*)dig, (int)B, kN, 16, n, sums);
-    auto k = pl.slices > 1 ? ks_mfma8_kernel<KM_CT, true> : ks_mfma8_kernel<KM_CT, false>;
+    auto k = ks_mfma8_kernel<KM_CT, false>;
+    if constexpr (KM_CT == 2) k = pl.slices > 1 ? ks_mfma8_kernel<2, true> : k;
     hipLaunchKernelGGL(k, dim3(8 * pl.per), dim3(THREADS), 0, s, big, (const uint4*)dig, (const int8_t*)c->d_ksk8,
                        sums ? sums : o.out, sums ? nullptr : o.ptrs, (int)B, n, kN, c->ks_wp, pl);
     launch_ks_store(o, pl.slices, B, n, s);
@@ -614,14 +616,16 @@ int launch_mfma_ct(tfhe_ctx* c, const uint32_t* big, D* dig, const KsOut<uint32_
     KsPlace pl;
     pl.tiles = (c->ks_wp / 16 + TW - 1) / TW;
     pl.groups = (int)((B + 64 * KM_CT - 1) / (64 * KM_CT));
-    pl.slices = ks_slices(c, pl.tiles * pl.groups, kN * t * V / 64, 4);
+    // (4 tiles per wave are taken where they fill the CUs: one slice)
+    pl.slices = KM_CT == 2 ? ks_slices(c, pl.tiles * pl.groups, kN * t * V / 64, 4) : 1;
     pl.per = (pl.tiles * pl.groups * pl.slices + 7) / 8;
     uint32_t* const sums = ks_sum_rows(o, pl.slices);
     hipLaunchKernelGGL((ks_digits_kernel<uint32_t, D>), dim3((kN + 63) / 64, (B + 63) / 64), dim3(THREADS), 0, s,
                        big, dig, (int)B, kN, t * bb, n, sums);
     const double table = 4.0 * c->ks_wp * kN * t * V, inputs = (double)B * kN * sizeof(D);
     pl.tile_major = table > inputs ? 1 : 0;
-    auto k = pl.slices > 1 ? ks_mfma_kernel<V, D, TW, KM_CT, true> : ks_mfma_kernel<V, D, TW, KM_CT, false>;
+    auto k = ks_mfma_kernel<V, D, TW, KM_CT, false>;
+    if constexpr (KM_CT == 2) k = pl.slices > 1 ? ks_mfma_kernel<V, D, TW, 2, true> : k;
     hipLaunchKernelGGL(k, dim3(8 * pl.per), dim3(THREADS), 0, s, big, (const D*)dig,
                        (const int8_t*)c->d_ksk8, sums ? sums : o.out, sums ? nullptr : o.ptrs, (int)B, n, kN, t, bb,
                        c->ks_wp, pl);
