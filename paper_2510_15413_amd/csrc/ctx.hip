@@ -594,32 +594,50 @@ __global__ void ksk_kernel(uint64_t Km, uint64_t Kn, T* ksk, const T* sx, const 
     }
 }
 
-// One wave per ciphertext: lanes take the mask words in turn (whole lines are
-// written, where a thread per ciphertext wrote 64 rows a word apart); the body
-// is their sum over the wave.  Bounded by the
-// integer multiplies of the stream (two 64-bit ones per word): 20,000
-// ciphertexts of n = 630 take 22 us (138 us with a thread per ciphertext, of
-// which 77 took 125 us; now 13 us).
-template <typename T>
+// G lanes per ciphertext: they take the mask words in turn (whole lines are
+// written, where a thread per ciphertext writes rows a word apart); the body is
+// their sum.  Bounded by the integer multiplies of the stream (two 64-bit ones per
+// word, and twelve for a ciphertext's noise, which one of its lanes forms while
+// the others wait), so the lanes follow the dimension: 10^6 ciphertexts of 32-bit
+// words in us by 1 / 4 / 16 / 64 lanes: dimension 8 28 / 29 / 92 / 351, 10 40 / 32
+// / 91 / 352, 32 146 / 80 / 100 / 353, 48 215 / 114 / 110 / 353, 64 284 / 150 / 119
+// / 354.  At 630, 64 ciphertexts take 43 / 21 / 7.1 / 4.2 us and 20,000 105 / 31 /
+// 17 / 20 (125 and 137 by threads whose words the compiler left in order).
+template <typename T, int G>
 __global__ __launch_bounds__(256) void lwe_encrypt_kernel(uint64_t Km, uint64_t Kn, int sigma, uint64_t start,
                                                           const T* __restrict__ key, const T* __restrict__ mu, T* out,
                                                           uint64_t count, int dim) {
-    const int lane = threadIdx.x & 63;
-    for (uint64_t c = blockIdx.x * 4ull + (threadIdx.x >> 6); c < count; c += gridDim.x * 4ull) {
+    constexpr int PER = 256 / G;  // ciphertexts per workgroup
+    const int lane = threadIdx.x & (G - 1);
+    for (uint64_t c = blockIdx.x * (uint64_t)PER + threadIdx.x / G; c < count; c += gridDim.x * (uint64_t)PER) {
         T* ct = out + c * (dim + 1);
         const uint64_t base = (start + c) * dim;
         T b = 0;
-        for (int w = lane; w < dim; w += 64) {
+        for (int w = lane; w < dim; w += G) {
             const T a = stream_torus<T>(Km, base + w);
             ct[w] = a;
             b += a * key[w];
         }
-        for (int o = 32; o > 0; o >>= 1) b += __shfl_xor(b, o);
+#pragma unroll
+        for (int o = G / 2; o > 0; o >>= 1) b += __shfl_xor(b, o);
         if (lane == 0) ct[dim] = stream_noise<T>(Kn, start + c, sigma) + mu[c] + b;
     }
 }
 
-// One wave per ciphertext: phase = b - <a, key>.
+template <typename T, int G>
+void launch_encrypt(uint64_t Km, uint64_t Kn, int sigma, uint64_t start, const void* key, const void* mu, void* out,
+                    uint64_t count, int dim, hipStream_t s) {
+    const unsigned grid = (unsigned)std::min<uint64_t>((count + 256 / G - 1) / (256 / G), 1u << 20);
+    hipLaunchKernelGGL((lwe_encrypt_kernel<T, G>), dim3(grid), dim3(256), 0, s, Km, Kn, sigma, start, (const T*)key,
+                       (const T*)mu, (T*)out, count, dim);
+}
+
+template <typename T>
+auto encrypt_launcher(uint32_t dim) {
+    return dim <= 8 ? launch_encrypt<T, 1> : dim <= 32 ? launch_encrypt<T, 4> : dim <= 64 ? launch_encrypt<T, 16>
+                                                                                          : launch_encrypt<T, 64>;
+}
+
 template <typename T>
 __global__ void lwe_phase_kernel(const T* key, const T* cts, T* out, uint64_t count, int dim) {
     const uint64_t c = blockIdx.x * 4ull + (threadIdx.x >> 6);
@@ -675,13 +693,8 @@ extern "C" int tfhe_lwe_encrypt(const tfhe_params* p, uint64_t seed, uint64_t ma
     if (!count) return TFHE_OK;
     hipStream_t st = (hipStream_t)stream;
     const uint64_t Km = stream_key(seed, mask_tag), Kn = stream_key(seed, noise_tag);
-    const unsigned grid = (unsigned)std::min<uint64_t>((count + 3) / 4, 1u << 20);
-    if (p->torus_bits == 32)
-        hipLaunchKernelGGL(lwe_encrypt_kernel<uint32_t>, dim3(grid), dim3(256), 0, st, Km, Kn, (int)sigma_log2, start,
-                           (const uint32_t*)d_key, (const uint32_t*)d_mu, (uint32_t*)d_out, count, (int)dim);
-    else
-        hipLaunchKernelGGL(lwe_encrypt_kernel<uint64_t>, dim3(grid), dim3(256), 0, st, Km, Kn, (int)sigma_log2, start,
-                           (const uint64_t*)d_key, (const uint64_t*)d_mu, (uint64_t*)d_out, count, (int)dim);
+    const auto launch = p->torus_bits == 32 ? encrypt_launcher<uint32_t>(dim) : encrypt_launcher<uint64_t>(dim);
+    launch(Km, Kn, (int)sigma_log2, start, d_key, d_mu, d_out, count, (int)dim, st);
     return hipGetLastError() == hipSuccess ? TFHE_OK : TFHE_EHIP;
 }
 
