@@ -168,7 +168,9 @@ int tfhe_set_kernel(tfhe_ctx* ctx, int kind);
  *                        batches: SUM-tree levels, server ticks) instead of
  *                        one workgroup per group for all n steps; -1 (the
  *                        default) = half the device's CUs for N >= 512 and
- *                        never for N = 256, 0 = never. */
+ *                        never for N = 256, 0 = never.  Where the transforms
+ *                        run (a context with spectra, the default row pass
+ *                        and digit grouping) only a positive value does. */
 #define TFHE_TUNE_SPLIT_GROUPS 4
 int tfhe_set_tuning(tfhe_ctx* ctx, int key, int64_t value);
 /* Current value of a tuning knob (as set, 0 or -1 for the defaults). */

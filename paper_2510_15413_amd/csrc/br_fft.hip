@@ -35,6 +35,12 @@
 // ciphertexts and outputs of its workgroup, and each key value read from
 // memory serves G ciphertexts.  The inverse runs the same steps backwards.
 // A butterfly is 6 fused multiply-adds (x +- w y with w = c (1 + i t)).
+// Published methods used: the folding of a real polynomial mod X^N + 1 into N/2
+// complex points (a weighted transform: Crandall and Fagin, "Discrete weighted
+// transforms and large-integer arithmetic", Math. Comp. 62, 1994) and twiddles as
+// cosine and tangent for fused multiply-adds (Linzer and Feig, "Implementation of
+// efficient FFT algorithms on fused multiply-add architectures", IEEE Trans.
+// Signal Processing 41, 1993).
 //
 // Workgroup: G ciphertexts, W waves, W/G polynomials of each at a time; the
 // accumulators stay in LDS, natural order, for all n steps.

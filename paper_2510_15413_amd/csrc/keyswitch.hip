@@ -108,6 +108,7 @@ __global__ __launch_bounds__(THREADS) void ks_digits_kernel(const T* __restrict_
 }
 
 // The sliced sums [B][n+1] to the ciphertexts' output addresses, a wave each.
+// (About 6 us of a level, most of it the launch: one gate 2.397 -> 2.403 ms.)
 template <typename T>
 __global__ __launch_bounds__(THREADS) void ks_store_kernel(const T* __restrict__ sums, const uint64_t* out_ptrs, int B,
                                                            int n) {
